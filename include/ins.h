@@ -482,8 +482,9 @@ ins_status ins_face_filter(ins_ctx ctx, const void* u, int factor, void* u_coars
  * unnormalised DFT), k = 0 .. nbins-1, per field of the batch. e: device
  * float64 array [batch][nbins], overwritten; shells beyond nbins are dropped
  * (nbins = floor(sqrt(dim) * n_max / 2 + 1/2) + 1 keeps every mode, so the sum
- * of e equals the mean kinetic energy). Uses the context's spectrum buffer;
- * shell sums are accumulated with atomic adds (order-dependent rounding). */
+ * of e equals the mean kinetic energy). Uses the context's spectrum and pressure
+ * buffers; each workgroup sums its shells in LDS with atomic adds
+ * (order-dependent rounding). */
 ins_status ins_energy_spectrum(ins_ctx ctx, const void* u, double* e, int nbins);
 
 /* ---------------------------------------------------------------------------

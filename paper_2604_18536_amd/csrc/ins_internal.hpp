@@ -218,7 +218,10 @@ hipError_t launch_eddy_backward(const Grid& g, const T* u, const T* nu, const T*
 template <typename T>
 hipError_t launch_face_filter(const Grid& fine, int f, const T* u, T* uc, hipStream_t s);
 // Accumulate 1/2 |X|^2 / N^2 of one half spectrum into integer-|k| shells (atomic adds).
-hipError_t launch_spectrum_bins(const Grid& g, const cd* spec, double* bins, int nbins, hipStream_t s);
+// bins[b][k] (+)= shell k of field b's half spectrum (first: overwritten); part:
+// scratch of part_doubles values for the partial rows of the shell sums.
+hipError_t launch_spectrum_bins(const Grid& g, const cd* spec, double* part, size_t part_doubles, double* bins,
+                                int nbins, bool first, hipStream_t s);
 // p[0..n) = 0 with a kernel (kept out of hipMemsetAsync so callers may capture it).
 hipError_t launch_fill_zero(double* p, size_t n, hipStream_t s);
 hipError_t launch_fill_zero_f(float* p, size_t n, hipStream_t s);

@@ -1748,7 +1748,6 @@ ins_status ins_energy_spectrum(ins_ctx ctx, const void* u, double* e, int nbins)
         need(e, "e");
         if (nbins < 1) raise(INS_ERR_INVALID, "nbins must be >= 1");
         const ins::Grid& g = ctx->g;
-        ctx->launch("fill_zero", [&] { return ins::launch_fill_zero(e, size_t(nbins) * g.batch, ctx->stream); });
         for (int a = 0; a < g.dim; ++a) {
             with_type(ctx, [&](auto tag) {
                 using T = decltype(tag);
@@ -1760,7 +1759,10 @@ ins_status ins_energy_spectrum(ins_ctx ctx, const void* u, double* e, int nbins)
             ctx->launch("fft_y_fwd", [&] { return ins::launch_fft_strided(g, ctx->spec, ctx->py, ctx->py, 1, 0, ctx->lnl_y, ctx->st, ctx->stream); });
             if (g.dim == 3)
                 ctx->launch("fft_z_fwd", [&] { return ins::launch_fft_strided(g, ctx->spec, ctx->pz, ctx->pz, 2, 0, ctx->lnl_z, ctx->st, ctx->stream); });
-            ctx->launch("spectrum_bins", [&] { return ins::launch_spectrum_bins(g, ctx->spec, e, nbins, ctx->stream); });
+            ctx->launch("spectrum_bins", [&] {
+                return ins::launch_spectrum_bins(g, ctx->spec, ctx->p, ctx->scal_bytes() / sizeof(double), e, nbins,
+                                                 a == 0, ctx->stream);
+            });
         }
     });
 }
