@@ -62,7 +62,7 @@
  * Streams. Every call enqueues its kernels on the context's stream
  * (default: the null stream) and returns without a host synchronisation,
  * except where a host scalar is returned (ins_stats, ins_profile_*, ins_cg_info),
- * in ins_set_y_faces, and in the channel's CG pressure solves, which read their
+ * in ins_set_y_faces, and in the CG pressure solves of large fields, which read their
  * convergence flags every check_every iterations (ins_cg_set; 0 turns it off).
  *
  * Aliasing. Outputs must not alias inputs, except where an entry point says
@@ -137,7 +137,8 @@ typedef struct {
  * nu >= 0 is the kinematic viscosity of the diffusion term. Allocates the
  * forward workspace: stage registers (3 velocity fields), pressure, the half
  * spectrum (periodic grid, and the channel when its direct solver applies) and
- * three CG pressure-point fields (channel). */
+ * three CG pressure-point fields and the CG's exchange buffer (channel; at most 24
+ * bytes per cell and a few megabytes). */
 ins_status ins_create(const ins_grid* grid, ins_bc bc, double nu, ins_dtype dtype, ins_ctx* out);
 ins_status ins_destroy(ins_ctx ctx);
 /* stream: a hipStream_t (NULL = null stream). */
@@ -169,7 +170,9 @@ const char* ins_last_error(void);
  * divergence of the gradient without assembling it (Sec. 2.6.1 iterative
  * solver), from p = 0, for A p = mean(r) - r, independently per batch field.
  * A field stops once ||res|| <= rtol ||res_0|| (res the recursively updated
- * residual) or after maxiter iterations. Iterations run back to back on the
+ * residual) or after maxiter iterations. A field that fits on the chip (about
+ * 500,000 cells) is solved by one launch, which stops by itself (check_every is
+ * not used). Otherwise iterations run back to back on the
  * stream; every check_every iterations the call reads the convergence flags
  * to the host once (a stream synchronisation), and stops launching when all
  * fields are done. check_every = 0 never synchronises and always launches

@@ -299,6 +299,23 @@ hipError_t launch_cg_update(const Grid& g, double* r, const double* p, const dou
                             double* rbn, CgScal* st, int k, double rtol2, int maxiter, hipStream_t s);
 // st.rr / st.relres from the newest rr partials.
 hipError_t launch_cg_finish(const Grid& g, const double* rb, CgScal* st, hipStream_t s);
+// The whole iteration in one launch where a field fits on the chip (k_cgsolve.hip):
+// G workgroups per field (0: it does not fit; 1: no exchange between workgroups) of
+// nt threads with c cells each along the last direction, nb[a] blocks of b[a] cells
+// per direction, outboxes of face slots, `fields` fields per launch.
+constexpr int kCgMaxGroups = 64;
+constexpr size_t kCgLdsMax = 98304, kCgLdsMulti = 160000;
+struct CgPlan {
+    int dim, G, nt, c, face, fields;
+    int nb[3], b[3];
+    // 8-byte words one field exchanges through
+    __host__ __device__ size_t words() const { return size_t(G) * (2 * dim * face * 2 + 8) * 2; }
+};
+CgPlan cg_plan(const Grid& g, int cus);
+// From r = b (x_0 = 0) and the partial sums rb0 of b.b: x and st of every field.
+// exch: P.words() * P.fields words (unused when P.G == 1).
+hipError_t launch_cg_solve(const Grid& g, const CgPlan& P, const double* r, double* x, const double* rb0, CgScal* st,
+                           void* exch, double rtol2, int maxiter, hipStream_t s);
 // t = w_j (t - mean_w(t)) in place (msum: partial-sum scratch).
 hipError_t launch_cg_weighted_center(const Grid& g, double* t, double* msum, double wsum, hipStream_t s);
 

@@ -213,6 +213,8 @@ struct ins_ctx_s {
     double* cg_part = nullptr;  // partial sums: mean, rr and p.q (two generations each); cg_blocks * batch each
     ins::CgScal* cg_st = nullptr;
     ins::CgScal* cg_host = nullptr;  // pinned host copy of cg_st
+    ins::CgPlan cg_pl{};             // single-launch solve (G = 0: the field does not fit)
+    void* cg_exch = nullptr;         // words its workgroups exchange through
     double* d_ym = nullptr;          // y metrics of the channel grid (Grid::ym)
     // stretched grid (a periodic direction, or the channel's x or z, given faces):
     // every operator from the per-direction metrics Grid::gm, pressure by CG
@@ -505,6 +507,14 @@ void upload_gen_metrics(ins_ctx c) {
     c->wsum = vol;
 }
 
+// Plan and exchange buffer of the single-launch solve (it depends on the sizes alone).
+void setup_cg_plan(ins_ctx c) {
+    int cus = 0;
+    hip_check(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, c->device), "hipDeviceGetAttribute");
+    c->cg_pl = ins::cg_plan(c->g, cus);
+    if (c->cg_pl.G > 1) c->cg_exch = c->alloc(c->cg_pl.words() * c->cg_pl.fields * sizeof(unsigned long long));
+}
+
 // Switch a context to the stretched-grid operators (irreversible): the CG
 // workspace of the pressure solve is allocated here for a periodic context.
 void enter_gen(ins_ctx c) {
@@ -520,6 +530,7 @@ void enter_gen(ins_ctx c) {
         hip_check(hipMemset(c->cg_st, 0, size_t(g.batch) * sizeof(ins::CgScal)), "hipMemset");
         hip_check(hipHostMalloc(reinterpret_cast<void**>(&c->cg_host), size_t(g.batch) * sizeof(ins::CgScal)),
                   "hipHostMalloc");
+        setup_cg_plan(c);
     }
     c->use_direct = false;
     c->direct_ok = false;
@@ -566,6 +577,13 @@ void cg_solve(ins_ctx c, const void* vel, const double* r, double* x, int mode) 
         return ins::launch_cg_init(g, c->cg_r, x, msum, rb[0], c->cg_st, mode, c->wsum, c->stream);
     });
     const double rtol2 = c->cg_rtol * c->cg_rtol;
+    if (c->cg_pl.G > 0) {
+        c->launch("cg_solve", [&] {
+            return ins::launch_cg_solve(g, c->cg_pl, c->cg_r, x, rb[0], c->cg_st, c->cg_exch, rtol2, c->cg_maxiter,
+                                        c->stream);
+        });
+        return;
+    }
     auto apply = [&](int k) {
         c->launch("cg_apply", [&] {
             return ins::launch_cg_apply(g, c->cg_r, c->cg_p[k & 1], c->cg_p[(k + 1) & 1], x, rb[k & 1],
@@ -1227,6 +1245,7 @@ ins_status ins_create(const ins_grid* grid, ins_bc bc, double nu, ins_dtype dtyp
             hip_check(hipMemset(c->cg_st, 0, size_t(g.batch) * sizeof(ins::CgScal)), "hipMemset");
             hip_check(hipHostMalloc(reinterpret_cast<void**>(&c->cg_host), size_t(g.batch) * sizeof(ins::CgScal)),
                       "hipHostMalloc");
+            setup_cg_plan(c);
             c->p = static_cast<double*>(c->alloc(c->scal_bytes()));
             c->ry = c->alloc(c->vel_bytes());
             c->wa = c->alloc(c->vel_bytes());

@@ -1,0 +1,604 @@
+// Conjugate-gradient solve of one field in one launch (channel and stretched
+// grids whose field fits on the chip): the residual, the solution, A p and the
+// operator's coefficients of a workgroup's block of cells live in registers, the
+// search direction with a one-cell halo in LDS, for all iterations.
+//
+// Why: a 4096-cell field took two launches of 5-6 us per iteration, a 238k-cell
+// field 13 + 10 us, for 0.1-6 MB of data: launch, fill and drain, and every
+// workgroup's re-reduction of the partial sums. What bounds it here is latency:
+// that of the sums, and of the stencil's LDS reads at 2 waves per SIMD. Per iteration
+// (before -> now, one step's four solves): 64^2 12 -> 1.6 us, 128^2 2.8, 32^3 3.2,
+// 70 x 63 x 54 23.5 -> 5.8, the channel 66 x 81 x 48 24 -> 6.1, 79^3 26 -> 11 us.
+//
+// One workgroup (fields of at most 4096 cells): the recurrence, stop test and sums
+// of k_cg.hpp, two sums per iteration. Several workgroups: one exchange per
+// iteration instead of two. p.q, r.q, q.q and r.r are summed together and the
+// boundary of q = A p travels with them (the halo's r and p follow the recurrence
+// locally); beta needs rr_{k+1} before it is summed and takes
+// |r - alpha q|^2 = rr_k - 2 alpha r.q + alpha^2 q.q, while alpha and the stop test
+// use the summed r.r, one exchange later. The split depends on the field's sizes
+// alone, so a field of a batch gives bitwise what it gives alone.
+//
+// Between workgroups. Every value that crosses workgroups (a partial sum, a
+// boundary value of A p) is one double sent as two 64-bit words {half, tag},
+// written and polled with device scope: a reader that sees the tag of the
+// iteration it waits for has the half that came with it, so no fence,
+// cache write-back or barrier counter is needed (a device-scope fence writes back
+// an XCD's L2). Tags count up within a launch, from slots zeroed by the launch
+// before. Even and odd iterations have slots of their own: those of iteration k
+// are rewritten in iteration k + 2, after the sums of iteration k + 1, which every
+// reader of the old values has entered by then.
+//
+// All workgroups of a launch have to be resident together. The launch is
+// cooperative, and the plan uses at most a quarter of the workgroups the chip
+// holds, so that launches from the process's four hardware queues fit side by
+// side (a cooperative launch recorded into a graph replays as a plain one).
+// Every wait is bounded all the same: past the bound the field becomes NaN.
+#include <algorithm>
+
+#include "k_cg.hpp"
+
+namespace ins {
+
+#define INS_AINLINE __attribute__((always_inline))
+
+namespace {
+
+using u64 = unsigned long long;
+
+// Halo cells per thread of an instance.
+constexpr int cg_halo(int c) { return c > 12 ? 6 : 4; }
+constexpr unsigned kCgpSpin = 1u << 25;   // polls before a wait gives up (about half a minute)
+
+typedef unsigned int v4u __attribute__((ext_vector_type(4)));
+typedef __amdgpu_buffer_rsrc_t Rsrc;
+
+// Device-scope buffer access (sc1: past the XCD's L2): what a relaxed device-scope
+// atomic is, 16 bytes at once. The empty asm in the polling loops keeps their loads
+// from being moved or merged (the volatile bit would make them system scope).
+constexpr int kDeviceScope = 16;
+
+__device__ __forceinline__ void post(Rsrc b, unsigned slot, unsigned tag, double v) {
+    const u64 u = static_cast<u64>(__double_as_longlong(v));
+    __builtin_amdgcn_raw_buffer_store_b128(v4u{unsigned(u >> 32), tag, unsigned(u), tag}, b, slot * 8u, 0, kDeviceScope);
+}
+__device__ __forceinline__ v4u peek(Rsrc b, unsigned slot) {
+    return __builtin_amdgcn_raw_buffer_load_b128(b, slot * 8u, 0, kDeviceScope);
+}
+__device__ __forceinline__ double value_of(v4u w) {
+    return __longlong_as_double(static_cast<long long>((u64(w.x) << 32) | w.z));
+}
+
+// Wait for this thread's N slots; all loads of a round go out together (no branch
+// between them). False: gave up.
+template <int N>
+__device__ __forceinline__ bool collect(Rsrc base, const unsigned (&slot)[N], unsigned off, unsigned tag, double (&v)[N]) {
+    for (unsigned n = 0; n < kCgpSpin; ++n) {
+        v4u w[N];
+        asm volatile("" ::: "memory");
+#pragma unroll
+        for (int i = 0; i < N; ++i) w[i] = peek(base, slot[i] + off);
+        bool all = true;
+#pragma unroll
+        for (int i = 0; i < N; ++i) {
+            all = all && w[i].y == tag && w[i].w == tag;
+            v[i] = value_of(w[i]);
+        }
+        if (all) return true;
+    }
+    return false;
+}
+
+// Lane l of the first wave waits for sum l & 3 of the workgroups l >> 2,
+// (l >> 2) + 16, ... (four slots of two words per workgroup) and adds them.
+__device__ __forceinline__ bool collect_sum(Rsrc base, unsigned off, int groups, unsigned tag, double& sum) {
+    constexpr int NP = kCgMaxGroups / 16;
+    const unsigned w0 = threadIdx.x >> 2;
+    const unsigned slot0 = off + 8 * min(w0, unsigned(groups) - 1u) + 2 * (threadIdx.x & 3);
+    for (unsigned n = 0; n < kCgpSpin; ++n) {
+        v4u w[NP];
+        asm volatile("" ::: "memory");
+#pragma unroll
+        for (int i = 0; i < NP; ++i)
+            w[i] = peek(base, int(w0) + 16 * i < groups ? slot0 + 128 * i : slot0);
+        bool all = true;
+        sum = 0.0;
+#pragma unroll
+        for (int i = 0; i < NP; ++i) {
+            all = all && w[i].y == tag && w[i].w == tag;
+            sum += int(w0) + 16 * i < groups ? value_of(w[i]) : 0.0;
+        }
+        if (all) return true;
+    }
+    return false;
+}
+
+// Sum over a wave, uniform: DPP adds within rows of 16, then across rows (the xor
+// shuffles of k_cg.hpp go through the LDS unit, six dependent trips per sum).
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double dpp_add(double v) {
+    const u64 b = static_cast<u64>(__double_as_longlong(v));
+    const unsigned lo = __builtin_amdgcn_update_dpp(0, int(unsigned(b)), CTRL, ROWS, 0xf, false);
+    const unsigned hi = __builtin_amdgcn_update_dpp(0, int(unsigned(b >> 32)), CTRL, ROWS, 0xf, false);
+    return v + __longlong_as_double(static_cast<long long>((u64(hi) << 32) | lo));
+}
+__device__ __forceinline__ double wave_total(double v) {
+    v = dpp_add<0x111, 0xf>(v);  // row_shr 1, 2, 4, 8: lane 15 of each row holds its sum
+    v = dpp_add<0x112, 0xf>(v);
+    v = dpp_add<0x114, 0xf>(v);
+    v = dpp_add<0x118, 0xf>(v);
+    v = dpp_add<0x142, 0xa>(v);  // row_bcast 15 into rows 1 and 3
+    v = dpp_add<0x143, 0xc>(v);  // row_bcast 31 into rows 2 and 3: lane 63 holds the total
+    const u64 b = static_cast<u64>(__double_as_longlong(v));
+    const unsigned lo = __builtin_amdgcn_readlane(int(unsigned(b)), 63);
+    const unsigned hi = __builtin_amdgcn_readlane(int(unsigned(b >> 32)), 63);
+    return __longlong_as_double(static_cast<long long>((u64(hi) << 32) | lo));
+}
+
+// Width w^a_i and 1 / d^a_i of direction a (i = -1 .. n - 1): a stretched grid's
+// metrics, the channel's y metrics, or the uniform spacing in the channel's
+// scaling (A = -w_y D G there: w = 1 and 1 / h^2 along x and z).
+__device__ __forceinline__ double met_w(const Grid& g, int a, int n, int i) {
+    if (g.gm[0]) return g.gm[a][3 * (n + 2) + i + 1];
+    return a == 1 ? g.ym[3 * (n + 2) + i] : 1.0;
+}
+__device__ __forceinline__ double met_id(const Grid& g, int a, int n, int i) {
+    if (g.gm[0]) return g.gm[a][(n + 2) + i + 1];
+    return a == 1 ? g.ym[(n + 2) + i + 1] : g.ih2[a];
+}
+
+}  // namespace
+
+// NT threads, C consecutive cells each along the last direction (z; y in 2D):
+// their neighbours along it are mostly in the thread's own registers, the lateral
+// coefficients are constants of the thread, those of the last direction come from
+// an LDS table. MULTI: several workgroups per field.
+template <int NT, int C, int DIM, bool MULTI>
+__global__ __launch_bounds__(NT, 2) void k_cg_solve(Grid g, CgPlan P, const double* __restrict__ r0,
+                                                  double* __restrict__ x, const double* __restrict__ rb0,
+                                                  CgScal* __restrict__ st, u64* __restrict__ ex, int field0,
+                                                  double rtol2, int maxiter) {
+    // p on the block plus halo, the table of the last direction, (MULTI) q on the block
+    extern __shared__ double pl[];
+    __shared__ double sh[NT / 64][4], tot[4];
+    __shared__ int lost;
+    constexpr int NW = NT / 64, HALO = cg_halo(C);
+    constexpr int M = DIM - 1;  // the last direction
+    const int tid = threadIdx.x;
+    const int fs = blockIdx.x / P.G;  // field of this launch
+    const int f = field0 + fs;
+    const int wg = blockIdx.x - fs * P.G;
+    const int n[3] = {g.nx, g.ny, g.nz};
+    const int bc[3] = {wg % P.nb[0], (wg / P.nb[0]) % P.nb[1], wg / (P.nb[0] * P.nb[1])};
+    int o[3], e[3];  // origin and extent of the block
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        o[a] = bc[a] * P.b[a];
+        e[a] = min(P.b[a], n[a] - o[a]);
+    }
+    const int sy = P.b[0] + 2, sz = sy * (P.b[1] + 2);
+    const int st3[3] = {1, sy, sz};
+    const int sm = st3[M];
+    const int npl = sz * (DIM == 3 ? P.b[2] + 2 : 1);
+    const bool wally = g.ywalls || !g.gm[0];  // no faces beyond the first and last row
+    for (int i = tid; i < npl; i += NT) pl[i] = 0.0;
+    double* tw = pl + npl;        // w of the last direction's cells
+    double* td = tw + P.b[M];     // 1 / d of their lower faces, then of the last upper one (0 at a wall)
+    double* ql = td + P.b[M] + 1;
+    for (int i = tid; i <= e[M]; i += NT) {
+        if (i < e[M]) tw[i] = met_w(g, M, n[M], o[M] + i);
+        const bool wall = M == 1 && wally && (o[M] + i == 0 || o[M] + i == n[M]);
+        td[i] = wall ? 0.0 : met_id(g, M, n[M], o[M] + i - 1);
+    }
+    if (tid == 0) lost = 0;
+
+    // words of this field, for even and odd iterations: P.G * 2 * DIM outboxes of
+    // P.face slots, then the four partial sums of each workgroup
+    const Rsrc fx = __builtin_amdgcn_make_buffer_rsrc(ex + size_t(fs) * P.words(), 0, int(P.words() * sizeof(u64)), 0x00027000);
+    const unsigned red = P.G * 2 * DIM * P.face * 2;
+    const unsigned half = unsigned(P.words() / 2);
+    auto outbox = [&](int w, int face) { return unsigned((w * 2 * DIM + face) * P.face * 2); };
+
+    // this thread's column: lateral cell (lx, ly) and the run c0 .. c0 + C - 1 of the last direction
+    const int lx = tid % e[0];
+    const int ly = DIM == 3 ? (tid / e[0]) % e[1] : 0;
+    // (a thread without cells reads, and never writes, the block's first ones)
+    int c0 = (DIM == 3 ? tid / (e[0] * e[1]) : tid / e[0]) * C;
+    const bool idle = c0 >= e[M];
+    if (idle) c0 = 0;
+    const int nc = idle ? 0 : min(C, e[M] - c0);  // cells of this thread
+    const int nl = max(nc - 1, 0);
+    const int gx = o[0] + lx, gy = o[1] + ly;
+    const int cell0 = (lx + 1) + (DIM == 3 ? (ly + 1) * sy : 0) + (c0 + 1) * sm;
+    const int rm = DIM == 3 ? P.b[0] * P.b[1] : P.b[0];
+    const int ql0 = lx + (DIM == 3 ? ly * P.b[0] : 0) + c0 * rm;
+    // lateral neighbours: a direction of one block wraps inside it (beyond a wall: the halo row, always 0)
+    const int xm = (P.nb[0] == 1 && lx == 0) ? e[0] - 1 : -1, xp = (P.nb[0] == 1 && lx == e[0] - 1) ? 1 - e[0] : 1;
+    const bool ywrap = DIM == 3 && P.nb[1] == 1 && !wally;
+    const int ym = (ywrap && ly == 0) ? (e[1] - 1) * sy : -sy, yp = (ywrap && ly == e[1] - 1) ? (1 - e[1]) * sy : sy;
+    const bool mwrap = P.nb[M] == 1 && !(M == 1 && wally);
+    const int mlo = (mwrap && c0 == 0) ? (e[M] - 1) * sm : -sm;
+    const int mhi = (mwrap && c0 + nl == e[M] - 1) ? (1 - e[M]) * sm : sm;  // of the run's last cell
+    const double wx = met_w(g, 0, n[0], gx), wy = DIM == 3 ? met_w(g, 1, n[1], gy) : 1.0;
+    const double axm = wy * met_id(g, 0, n[0], gx - 1), axp = wy * met_id(g, 0, n[0], gx);
+    double aym = 0.0, ayp = 0.0;
+    if constexpr (DIM == 3) {
+        if (!(wally && gy == 0)) aym = wx * met_id(g, 1, n[1], gy - 1);
+        if (!(wally && gy == g.ny - 1)) ayp = wx * met_id(g, 1, n[1], gy);
+    }
+    const double am = wx * wy;
+    const int64_t foff = int64_t(f) * g.ncell;
+    const int64_t gm = DIM == 3 ? int64_t(g.ny) * g.nx : g.nx;  // stride of the last direction
+    const int64_t g0 = foff + gx + (DIM == 3 ? int64_t(gy) * g.nx : 0) + (o[M] + c0) * gm;
+    double r[C], xs[C], p[C], q[MULTI ? 1 : C];  // MULTI: q, whose boundary is sent on, lives in LDS
+#pragma unroll
+    for (int j = 0; j < C; ++j) {
+        r[j] = j < nc ? r0[g0 + j * gm] : 0.0;
+        xs[j] = 0.0;
+        p[j] = r[j];
+    }
+
+    // the table's entries of this thread's cells, where the registers allow it
+    // (0 past the thread's run, so that its cells' loads and sums need no branch; the
+    // longest runs keep the branch and the LDS table: they spill otherwise)
+    constexpr bool TREG = C <= 12;
+    double twr[TREG ? C : 1], tdr[TREG ? C + 1 : 1];
+    auto tw_of = [&](int j) { return TREG ? twr[TREG ? j : 0] : tw[c0 + j]; };
+    auto td_of = [&](int j) { return TREG ? tdr[TREG ? j : 0] : td[c0 + j]; };
+
+    // halo cells of this thread: their LDS index, the slot they come from, and (the
+    // same face seen from inside) the boundary cell to send and its slot
+    int hl[HALO], hb[HALO];
+    unsigned hs[HALO], ho[HALO];
+    double hr[HALO];  // r there
+    if constexpr (MULTI) {
+#pragma unroll
+        for (int h = 0; h < HALO; ++h) {
+            hl[h] = -1;
+            hb[h] = 0;
+            hs[h] = ho[h] = red + 8 * wg;  // none: its own sum, there in any case
+            hr[h] = 0.0;
+            int k = (NT - 1 - tid) + h * NT;  // the first wave, which collects the sums, last
+#pragma unroll
+            for (int a = 0; a < DIM; ++a) {
+                if (P.nb[a] == 1) continue;
+                const int a1 = a == 0 ? 1 : 0, a2 = a == 2 ? 1 : 2;
+                const int size = e[a1] * e[a2];
+#pragma unroll
+                for (int s = 0; s < 2; ++s) {
+                    if (a == 1 && wally && bc[1] == (s ? P.nb[1] - 1 : 0)) continue;
+                    if (k >= 0 && k < size) {
+                        const int i1 = k % e[a1], i2 = k / e[a1];
+                        int nbr[3] = {bc[0], bc[1], bc[2]};
+                        nbr[a] = s ? (bc[a] + 1 == P.nb[a] ? 0 : bc[a] + 1) : (bc[a] == 0 ? P.nb[a] - 1 : bc[a] - 1);
+                        const int w2 = (nbr[2] * P.nb[1] + nbr[1]) * P.nb[0] + nbr[0];
+                        hl[h] = (s ? e[a] + 1 : 0) * st3[a] + (i1 + 1) * st3[a1] + (DIM == 3 ? (i2 + 1) * st3[a2] : 0);
+                        hs[h] = outbox(w2, 2 * a + (1 - s)) + 2 * k;
+                        ho[h] = outbox(wg, 2 * a + s) + 2 * k;
+                        const int c[3] = {a == 0 ? (s ? e[0] - 1 : 0) : i1, a == 1 ? (s ? e[1] - 1 : 0) : (a == 0 ? i1 : i2),
+                                          a == 2 ? (s ? e[2] - 1 : 0) : i2};
+                        hb[h] = (c[2] * P.b[1] + c[1]) * P.b[0] + c[0];
+                        // r_0 comes from memory
+                        int c3[3];
+                        c3[a] = s ? o[a] + e[a] : o[a] - 1;
+                        c3[a] = c3[a] < 0 ? c3[a] + n[a] : (c3[a] >= n[a] ? c3[a] - n[a] : c3[a]);
+                        c3[a1] = o[a1] + i1;
+                        c3[a2] = o[a2] + i2;
+                        hr[h] = r0[foff + (int64_t(c3[2]) * g.ny + c3[1]) * g.nx + c3[0]];
+                    }
+                    k -= size;
+                }
+            }
+        }
+    }
+
+    // Sum over the workgroup, in every thread (the only one of its field); which: p.q or r.r
+    auto wg_sum = [&](double v, int which) {
+        v = wave_total(v);
+        if ((tid & 63) == 0) sh[tid >> 6][which] = v;
+        __syncthreads();
+        double s = 0.0;
+#pragma unroll
+        for (int i = 0; i < NW; ++i) s += sh[i][which];
+        return s;
+    };
+
+    // rr_0 from the partial sums of the kernel that formed r_0
+    double rr0;
+    {
+        const int np = cg_blocks_of(g);
+        double s = 0.0;
+        for (int i = tid; i < np; i += NT) s += rb0[int64_t(f) * np + i];
+        rr0 = block_sum<NT>(s, &sh[0][0]);  // synchronises: pl, the table and lost are set
+    }
+    if constexpr (TREG) {
+#pragma unroll
+        for (int j = 0; j < C; ++j) twr[j] = j < nc ? tw[c0 + j] : 0.0;
+#pragma unroll
+        for (int j = 0; j <= C; ++j) tdr[j] = j <= nc && nc > 0 ? td[c0 + j] : 0.0;
+    }
+    double rr = rr0;
+    int k = 0;
+    bool bad = false;
+    if (!cg_stopped(rr0, rr0, 0, rtol2, maxiter)) {
+#pragma unroll
+        for (int j = 0; j < C; ++j)
+            if (j < nc) pl[cell0 + j * sm] = p[j];
+        if constexpr (MULTI) {
+#pragma unroll
+            for (int h = 0; h < HALO; ++h)
+                if (hl[h] >= 0) pl[hl[h]] = hr[h];
+        }
+        for (;;) {
+            const unsigned tag = unsigned(k) + 1u;
+            const unsigned bx = (k & 1) ? half : 0u;
+            // keep the addresses below out of registers held across iterations
+            int cell = cell0, qb = ql0;
+            asm volatile("" : "+v"(cell), "+v"(qb));
+            __syncthreads();
+            // q = A p
+            double s4[4] = {0.0, 0.0, 0.0, 0.0};
+            const double pfirst = pl[cell + mlo], plast = pl[cell + nl * sm + mhi];
+#pragma unroll
+            for (int j = 0; j < C; ++j) {
+                auto cell_ap = [&]() INS_AINLINE {
+                    const int c = cell + (TREG ? min(j, nl) : j) * sm;
+                    const double pc = p[j];
+                    // along the last direction: registers but at the run's ends
+                    const double pm = j == 0 ? pfirst : p[j > 0 ? j - 1 : 0];
+                    const double pp = j == nl || j == C - 1 ? plast : p[j < C - 1 ? j + 1 : j];
+                    double lat = (pc - pl[c + xp]) * axp + (pc - pl[c + xm]) * axm;
+                    if constexpr (DIM == 3) lat += (pc - pl[c + yp]) * ayp + (pc - pl[c + ym]) * aym;
+                    const double v = tw_of(j) * lat + am * ((pc - pp) * td_of(j + 1) + (pc - pm) * td_of(j));
+                    s4[0] += pc * v;
+                    if constexpr (MULTI) {
+                        if (j < nc) ql[qb + j * rm] = v;
+                        s4[1] += r[j] * v;
+                        s4[2] += j < nc ? v * v : 0.0;
+                        s4[3] += r[j] * r[j];
+                    } else {
+                        q[j] = j < nc ? v : 0.0;
+                    }
+                };
+                if constexpr (TREG) cell_ap();
+                else if (j < nc) cell_ap();
+            }
+            if constexpr (!MULTI) {
+                const double pq = wg_sum(s4[0], 0);
+                if (!(pq > 0.0)) {  // no component outside the constants: ends without an update
+                    rr = 0.0;
+                    break;
+                }
+                const double alpha = rr / pq;
+                double acc = 0.0;
+#pragma unroll
+                for (int j = 0; j < C; ++j) {
+                    xs[j] += alpha * p[j];
+                    r[j] -= alpha * q[j];
+                    acc += r[j] * r[j];
+                }
+                const double rrm = rr;
+                rr = wg_sum(acc, 1);
+                ++k;
+                if (cg_stopped(rr, rr0, k, rtol2, maxiter)) break;
+                const double beta = rr / rrm;
+#pragma unroll
+                for (int j = 0; j < C; ++j) {
+                    p[j] = r[j] + beta * p[j];
+                    if (j < nc) pl[cell + j * sm] = p[j];
+                }
+            } else {
+                // totals over the field of p.q, r.q, q.q and r.r, in every thread; q at the halo
+#pragma unroll
+                for (int i = 0; i < 4; ++i) s4[i] = wave_total(s4[i]);
+                if ((tid & 63) == 0) {
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) sh[tid >> 6][i] = s4[i];
+                }
+                __syncthreads();
+                if (tid < 64) {
+                    if (tid < 4) {
+                        double s = 0.0;
+#pragma unroll
+                        for (int i = 0; i < NW; ++i) s += sh[i][tid];
+                        post(fx, bx + red + 8 * wg + 2 * tid, tag, s);
+                    }
+                    // lane l collects sum l & 3 of the workgroups l >> 2, (l >> 2) + 16, ...
+                    double t;
+                    if (!collect_sum(fx, bx + red, P.G, tag, t)) lost = 1;
+#pragma unroll
+                    for (int o = 4; o < 64; o <<= 1) t += __shfl_xor(t, o, 64);
+                    if (tid < 4) tot[tid] = t;
+                }
+                double hq[HALO];
+#pragma unroll
+                for (int h = 0; h < HALO; ++h) {
+                    hq[h] = 0.0;
+                    if (hl[h] >= 0) post(fx, bx + ho[h], tag, ql[hb[h]]);
+                }
+                if (!collect<HALO>(fx, hs, bx, tag, hq)) lost = 1;
+                __syncthreads();
+                if (lost) {
+                    bad = true;
+                    break;
+                }
+                rr = tot[3];
+                if (cg_stopped(rr, rr0, k, rtol2, maxiter)) break;
+                const double pq = tot[0];
+                if (!(pq > 0.0)) {
+                    rr = 0.0;
+                    break;
+                }
+                const double alpha = rr / pq;
+                // rr_{k+1} = |r - alpha q|^2, for beta alone: the next sums bring it as summed
+                const double beta = fmax(rr - alpha * (2.0 * tot[1] - alpha * tot[2]), 0.0) / rr;
+#pragma unroll
+                for (int j = 0; j < C; ++j) {
+                    auto cell_up = [&]() INS_AINLINE {
+                        const double v = ql[qb + (TREG ? min(j, nl) : j) * rm];
+                        xs[j] += alpha * p[j];
+                        if (j < nc) r[j] -= alpha * v;
+                        p[j] = r[j] + beta * p[j];
+                        if (j < nc) pl[cell + j * sm] = p[j];
+                    };
+                    if constexpr (TREG) cell_up();
+                    else if (j < nc) cell_up();
+                }
+#pragma unroll
+                for (int h = 0; h < HALO; ++h) {
+                    if (hl[h] >= 0) {
+                        hr[h] -= alpha * hq[h];
+                        pl[hl[h]] = hr[h] + beta * pl[hl[h]];
+                    }
+                }
+                ++k;
+            }
+        }
+    }
+    const double nan = __longlong_as_double(0x7ff8000000000000ll);
+#pragma unroll
+    for (int j = 0; j < C; ++j)
+        if (j < nc) x[g0 + j * gm] = bad ? nan : xs[j];
+    if (wg == 0 && tid == 0) {
+        CgScal& s = st[f];
+        s.rr = bad ? nan : rr;
+        s.rr0 = rr0;
+        s.relres = rr0 > 0.0 ? sqrt(s.rr / rr0) : 0.0;
+        s.it = k;
+        s.done = 1;
+    }
+}
+
+__global__ __launch_bounds__(kBlock) void k_cg_clear(u64* p, int64_t n) {
+    const int64_t i = int64_t(blockIdx.x) * kBlock + threadIdx.x;
+    if (i < n) p[i] = 0;
+}
+
+namespace {
+
+template <int NT, int C, int DIM, bool MULTI>
+const void* kernel_of() {
+    return reinterpret_cast<const void*>(&k_cg_solve<NT, C, DIM, MULTI>);
+}
+
+// The instance of a plan: threads and cells per thread.
+const void* cg_kernel(const Grid& g, const CgPlan& P) {
+#define INS_CGK(NT, C, MULTI) (g.dim == 3 ? kernel_of<NT, C, 3, MULTI>() : kernel_of<NT, C, 2, MULTI>())
+    if (P.G == 1) return P.nt == 256 ? INS_CGK(256, 4, false) : INS_CGK(512, 8, false);
+    switch (P.c) {
+        case 2: return INS_CGK(512, 2, true);
+        case 4: return INS_CGK(512, 4, true);
+        case 8: return INS_CGK(512, 8, true);
+        case 10: return INS_CGK(512, 10, true);
+        default: return INS_CGK(512, 20, true);
+    }
+#undef INS_CGK
+}
+
+size_t cg_lds(const Grid& g, const CgPlan& P) {
+    return (size_t(P.b[0] + 2) * (P.b[1] + 2) * (g.dim == 3 ? P.b[2] + 2 : 1) + 2 * P.b[g.dim - 1] + 1 +
+            (P.G > 1 ? size_t(P.b[0]) * P.b[1] * P.b[2] : 0)) *
+           sizeof(double);
+}
+
+// Threads a block of the plan needs: lateral cells times runs of c cells.
+int64_t cg_threads(const CgPlan& P) {
+    const int m = P.dim - 1;
+    return int64_t(P.b[0]) * (P.dim == 3 ? P.b[1] : 1) * ((P.b[m] + P.c - 1) / P.c);
+}
+
+}  // namespace
+
+// Plan of a field: G = 0 when it does not fit (the two-kernel iteration runs it).
+CgPlan cg_plan(const Grid& g, int cus) {
+    CgPlan P{};
+    P.dim = g.dim;
+    const int n[3] = {g.nx, g.ny, g.nz};
+    // one workgroup while a thread has at most 4 cells
+    P.G = 1;
+    for (int a = 0; a < 3; ++a) {
+        P.nb[a] = 1;
+        P.b[a] = n[a];
+    }
+    for (int nt : {256, 512}) {
+        P.nt = nt;
+        P.c = nt == 256 ? 4 : 8;
+        if (cg_threads(P) <= nt && cg_lds(g, P) <= kCgLdsMax) return P;
+    }
+    // several: the fewest cells per thread that a quarter of the chip's room allows
+    // (an iteration costs its two sums and C steps of the stencil), among those the
+    // split with the smallest halo
+    for (int c : {2, 4, 8, 10, 20}) {
+        CgPlan B{};
+        int64_t best = 0;
+        P.nt = 512;
+        P.c = c;
+        P.G = 2;
+        int per_cu = 0;
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, cg_kernel(g, P), P.nt, kCgLdsMulti) != hipSuccess) {
+            (void)hipGetLastError();
+            break;
+        }
+        const int gmax = std::min(kCgMaxGroups, per_cu * cus / 4);
+        for (int i = 1; i <= std::min(n[0], gmax); ++i) {
+            P.b[0] = (n[0] + i - 1) / i;
+            if ((n[0] + P.b[0] - 1) / P.b[0] != i) continue;
+            for (int j = 1; j <= n[1] && i * j <= gmax; ++j) {
+                P.b[1] = (n[1] + j - 1) / j;
+                if ((n[1] + P.b[1] - 1) / P.b[1] != j) continue;
+                for (int l = 1; l <= n[2] && i * j * l <= gmax; ++l) {
+                    P.b[2] = (n[2] + l - 1) / l;
+                    if ((n[2] + P.b[2] - 1) / P.b[2] != l) continue;
+                    if (cg_threads(P) > P.nt || cg_lds(g, P) > kCgLdsMulti) continue;
+                    int64_t halo = 0, face = 1;
+                    const int64_t area[3] = {int64_t(P.b[1]) * P.b[2], int64_t(P.b[0]) * P.b[2], int64_t(P.b[0]) * P.b[1]};
+                    const int nb[3] = {i, j, l};
+                    for (int a = 0; a < 3; ++a) {
+                        if (nb[a] == 1) continue;
+                        halo += 2 * area[a];
+                        face = std::max(face, area[a]);
+                    }
+                    if (i * j * l == 1 || halo > cg_halo(c) * P.nt || (B.G != 0 && halo >= best)) continue;
+                    best = halo;
+                    B = P;
+                    B.G = i * j * l;
+                    for (int a = 0; a < 3; ++a) B.nb[a] = nb[a];
+                    B.face = int(face);
+                }
+            }
+        }
+        if (B.G) {
+            B.fields = std::min(g.batch, per_cu * cus / (4 * B.G));
+            return B;
+        }
+    }
+    return CgPlan{};
+}
+
+hipError_t launch_cg_solve(const Grid& g, const CgPlan& P, const double* r, double* x, const double* rb0, CgScal* st,
+                           void* exch, double rtol2, int maxiter, hipStream_t s) {
+    Grid ga = g;
+    CgPlan pa = P;
+    u64* ex = static_cast<u64*>(exch);
+    const void* kern = cg_kernel(g, P);
+    const size_t lds = cg_lds(g, P);
+    const int step = P.G == 1 ? g.batch : P.fields;
+    for (int f0 = 0; f0 < g.batch; f0 += step) {
+        const int nf = std::min(step, g.batch - f0);
+        void* args[] = {&ga, &pa, &r, &x, &rb0, &st, &ex, &f0, &rtol2, &maxiter};
+        hipError_t e;
+        if (P.G == 1) {
+            e = hipLaunchKernel(kern, dim3(nf), dim3(P.nt), args, lds, s);
+        } else {
+            const int64_t words = int64_t(P.words()) * nf;
+            hipLaunchKernelGGL(k_cg_clear, dim3(int((words + kBlock - 1) / kBlock)), dim3(kBlock), 0, s, ex, words);
+            e = hipGetLastError();
+            if (e != hipSuccess) return e;
+            e = hipLaunchCooperativeKernel(kern, dim3(nf * P.G), dim3(P.nt), args, unsigned(lds), s);
+        }
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
+
+}  // namespace ins
