@@ -1100,12 +1100,24 @@ bool setup_fft(ins_ctx c, const std::vector<int>& rx, const std::vector<int>& ry
     auto strided_extra = [](int n, bool solve) {
         return static_cast<size_t>((n & 1) ? n : n / 2) * sizeof(cd) + (solve ? n * sizeof(double) : 0);
     };
-    c->lnl_x = choose_lines(c->px, 16, 8, kBlockHost, 0, false, 512);
-    c->lnl_y = channel ? 0 : choose_lines(c->py, 16, 8, 512, strided_extra(g.ny, d == 2), true);
+    // Small problems take fewer lines per workgroup, down to 2, until there is a
+    // workgroup per CU: with 16 lines the passes of a 256^2 field ran in 16
+    // workgroups, each as long as its chain of stages (one solve 27.9 -> 19.4 us;
+    // 4 x 256^2 28.4 -> 21.0, 1024^2 45.9 -> 39 us). From 256 workgroups on, more
+    // lines (longer runs) are better: 96 x 90 x 84 with a quarter of them 43.8 -> 58 us.
+    auto most_lines = [](int64_t lines) {
+        int m = 16;
+        while (m > 2 && lines / m < 256) m /= 2;
+        return m;
+    };
+    const int64_t nb = g.batch, half = g.nx / 2;
+    const int mx = most_lines(nb * g.nz * g.ny), my = most_lines(nb * g.nz * half), mz = most_lines(nb * g.ny * half);
+    c->lnl_x = choose_lines(c->px, mx, std::min(8, mx), kBlockHost, 0, false, 512);
+    c->lnl_y = channel ? 0 : choose_lines(c->py, my, std::min(8, my), 512, strided_extra(g.ny, d == 2), true);
     // the channel's z passes are plain forward / inverse transforms: 16-line batches
     // (256-byte runs) measured 13% faster there; the periodic fused z solve and the y
     // passes are faster with 8 lines of 256 threads
-    c->lnl_z = d == 3 ? choose_lines(c->pz, 16, channel ? 16 : 8, 512, strided_extra(g.nz, !channel), true) : 0;
+    c->lnl_z = d == 3 ? choose_lines(c->pz, mz, std::min(channel ? 16 : 8, mz), 512, strided_extra(g.nz, !channel), true) : 0;
     if (!channel) {
         ins::FftPlan& last = d == 3 ? c->pz : c->py;
         ins::FftPlan& rev = d == 3 ? c->pz_rev : c->py_rev;
