@@ -11,6 +11,7 @@
 // share through L2) instead of three times. With four ring slots the plane
 // being filled is never one being read, so one barrier per plane suffices.
 #include "k_common.hpp"
+#include "k_zmarch.hpp"
 
 namespace ins {
 
@@ -306,38 +307,24 @@ __global__ __launch_bounds__(TX * TY) void k_stage_zm(Grid g, const T* __restric
     }
 }
 
-// z planes per workgroup: long enough that the two extra halo planes are a
-// small overhead, short enough to give the chip at least `want` workgroups
-// (at most zmax planes, halved while there are fewer).
-int zm_chunk(const Grid& g, int tx, int ty, int want, int zmax) {
-    const int ntiles = ((g.nx + tx - 1) / tx) * ((g.ny + ty - 1) / ty) * g.batch;
-    int zc = zmax;
-    while (zc > 4 && int64_t(ntiles) * ((g.nz + zc - 1) / zc) < want) zc /= 2;
-    return zc;
-}
-
-// Reverse stage (32 x 8 tiles of 256 threads): 2048 workgroups, at most 32 planes.
-int zm_chunk(const Grid& g) { return zm_chunk(g, kZmTX, kZmTY, 2048, 32); }
-
-// Forward stage (64 x 8 tiles of 512 threads): one full wave of resident
-// workgroups, two per CU in float64 (128 VGPRs, 63 KB of LDS ring), four in
-// float32, up to 64 planes. Measured at 256^3: float64 64 planes (512
-// workgroups) 1.5% faster per step than 32; float32 32 planes (1024) 14%
-// faster than 64.
-int zm_chunk_stage(const Grid& g, bool fp64) { return zm_chunk(g, 64, 8, fp64 ? 512 : 1024, 64); }
-
 template <typename T, int TX, int TY, typename P = double>
 void launch_stage_zm_tile(const Grid& g, const T* w, const P* p, bool proj, const T* u0, T* y, int yinit,
                           double cy, T* wout, double cw, hipStream_t s, const T* mc, const T* wprev = nullptr,
                           double ry = 0.0, double rw = 0.0) {
-    const int zc = zm_chunk_stage(g, sizeof(T) == 8);
-    const int nblk = ((g.nx + TX - 1) / TX) * ((g.ny + TY - 1) / TY) * ((g.nz + zc - 1) / zc) * g.batch;
     // pointwise streams: u0 when it seeds the stage register or the accumulator,
     // y when the accumulator is read
     const int pt = ((wout || yinit) ? 1 : 0) | ((y && !yinit) ? 2 : 0);
-#define INS_SZM(PR, YWI, PTI, YI, RY, RW)                                                                          \
-    hipLaunchKernelGGL((k_stage_zm<T, PR, TX, TY, P, YWI, PTI>), dim3(nblk), dim3(TX * TY), 0, s, g, w, p, u0, y, YI, \
-                       T(cy), wout, T(cw), zc, mc, wprev, T(RY), T(RW))
+    // At most 64 planes (two more halo planes are then 3 % of the reads). float32
+    // counts 1024 workgroups, more than are resident (3 or 4 per CU): with 768 at
+    // 256^3 and 43 planes each the stages took 2-3 % longer than with 1024 and 32.
+#define INS_SZM(PR, YWI, PTI, YI, RY, RW)                                                                             \
+    do {                                                                                                              \
+        constexpr auto kern = &k_stage_zm<T, PR, TX, TY, P, YWI, PTI>;                                                \
+        const int zc = zm_chunk(g, TX, TY, sizeof(T) == 8 ? resident_groups<kern, TX * TY>() : 1024, 64);             \
+        const int nblk = ((g.nx + TX - 1) / TX) * ((g.ny + TY - 1) / TY) * ((g.nz + zc - 1) / zc) * g.batch;          \
+        hipLaunchKernelGGL((k_stage_zm<T, PR, TX, TY, P, YWI, PTI>), dim3(nblk), dim3(TX * TY), 0, s, g, w, p, u0, y, \
+                           YI, T(cy), wout, T(cw), zc, mc, wprev, T(RY), T(RW));                                      \
+    } while (0)
     if (wprev)
         INS_SZM(true, true, 3, 0, ry, rw);
     else if (!proj && pt == 3)
@@ -666,12 +653,16 @@ hipError_t launch_stage_vjp_zm(const Grid& g, const T* w, const double* p, bool 
                                const double* q, bool has_w, double cb, double cw, T* u0bar, int mode, T* ubar_out,
                                hipStream_t s, T* fbar_out) {
     if (has_w && cw == 0.0) return hipErrorInvalidValue;  // un - G q is recovered through 1 / cw
-    const int zc = zm_chunk(g);
-    const int nblk = ((g.nx + kZmTX - 1) / kZmTX) * ((g.ny + kZmTY - 1) / kZmTY) * ((g.nz + zc - 1) / zc) * g.batch;
     const T tb = T(cb), tw = T(cw);
-#define INS_VJP_ZM(PU, HW)                                                                                           \
-    hipLaunchKernelGGL((k_stage_vjp_zm<T, PU, HW>), dim3(nblk), dim3(kBlock), 0, s, g, w, p, ybar, un, q, tb, tw, u0bar, \
-                       mode, ubar_out, zc, fbar_out)
+#define INS_VJP_ZM(PU, HW)                                                                                            \
+    do {                                                                                                              \
+        constexpr auto kern = &k_stage_vjp_zm<T, PU, HW>;                                                             \
+        const int zc = zm_chunk(g, kZmTX, kZmTY, resident_groups<kern, kBlock>(), 32);                            \
+        const int nblk =                                                                                              \
+            ((g.nx + kZmTX - 1) / kZmTX) * ((g.ny + kZmTY - 1) / kZmTY) * ((g.nz + zc - 1) / zc) * g.batch;           \
+        hipLaunchKernelGGL((k_stage_vjp_zm<T, PU, HW>), dim3(nblk), dim3(kBlock), 0, s, g, w, p, ybar, un, q, tb, tw, \
+                           u0bar, mode, ubar_out, zc, fbar_out);                                                      \
+    } while (0)
     if (proj_u && has_w)
         INS_VJP_ZM(true, true);
     else if (proj_u)

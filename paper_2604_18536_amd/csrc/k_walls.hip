@@ -40,6 +40,7 @@
 // host and results are bitwise reproducible. A stopped field skips the work
 // of later iterations.
 #include "k_cg.hpp"
+#include "k_zmarch.hpp"
 #include "k_common.hpp"
 
 namespace ins {
@@ -1405,15 +1406,19 @@ hipError_t launch_wall_stage(const Grid& g, const T* w, const double* p, bool pr
                              double cy, T* wout, double cw, hipStream_t s) {
     if (g.dim == 3) {
         constexpr int TX = 64, TY = 8;
-        const int zc = zm_chunk_stage(g, sizeof(T) == 8);
-        const int nblk = ((g.nx + TX - 1) / TX) * ((g.ny + TY - 1) / TY) * ((g.nz + zc - 1) / zc) * g.batch;
         const int yi = yinit ? 1 : 0;
         // pointwise streams: u0 when it seeds the stage register or the
         // accumulator, y when the accumulator is read
         const int pt = ((wout || yinit) ? 1 : 0) | ((y && !yinit) ? 2 : 0);
 #define INS_WSZM(PR, PTI)                                                                                            \
-    hipLaunchKernelGGL((k_wall_stage_zm<T, PR, TX, TY, PTI>), dim3(nblk), dim3(TX * TY), 0, s, g, w, p, u0, y, yi, T(cy), \
-                       wout, T(cw), zc)
+    do {                                                                                                             \
+        constexpr auto kern = &k_wall_stage_zm<T, PR, TX, TY, PTI>;                                                  \
+        /* float32: at most 32 planes (512 x 256 x 256: stage 550 -> 505 us against 64) */                           \
+        const int zc = zm_chunk(g, TX, TY, resident_groups<kern, TX * TY>(), sizeof(T) == 8 ? 64 : 32);              \
+        const int nblk = ((g.nx + TX - 1) / TX) * ((g.ny + TY - 1) / TY) * ((g.nz + zc - 1) / zc) * g.batch;         \
+        hipLaunchKernelGGL((k_wall_stage_zm<T, PR, TX, TY, PTI>), dim3(nblk), dim3(TX * TY), 0, s, g, w, p, u0, y,   \
+                           yi, T(cy), wout, T(cw), zc);                                                              \
+    } while (0)
         if (proj && pt == 3)
             INS_WSZM(true, 3);
         else if (proj && pt == 2)
@@ -1453,13 +1458,16 @@ hipError_t launch_wall_stage_vjp(const Grid& g, const T* w, const double* p, boo
                                  const double* q, bool has_w, double cb, double cw, T* u0bar, int mode, T* ubar_out,
                                  hipStream_t s) {
     if (g.dim == 3) {
-        const int zc = zm_chunk(g, kWvTX, kWvTY, 2048, 32);
-        const int nblk =
-            ((g.nx + kWvTX - 1) / kWvTX) * ((g.ny + kWvTY - 1) / kWvTY) * ((g.nz + zc - 1) / zc) * g.batch;
         const T tb = T(cb), tw = T(cw);
-#define INS_WVJP_ZM(PU, HW)                                                                                       \
-    hipLaunchKernelGGL((k_wall_stage_vjp_zm<T, PU, HW>), dim3(nblk), dim3(kBlock), 0, s, g, w, p, ybar, un, q, tb, \
-                       tw, u0bar, mode, ubar_out, zc)
+#define INS_WVJP_ZM(PU, HW)                                                                                           \
+    do {                                                                                                              \
+        constexpr auto kern = &k_wall_stage_vjp_zm<T, PU, HW>;                                                        \
+        const int zc = zm_chunk(g, kWvTX, kWvTY, resident_groups<kern, kBlock>(), 32);                            \
+        const int nblk =                                                                                              \
+            ((g.nx + kWvTX - 1) / kWvTX) * ((g.ny + kWvTY - 1) / kWvTY) * ((g.nz + zc - 1) / zc) * g.batch;           \
+        hipLaunchKernelGGL((k_wall_stage_vjp_zm<T, PU, HW>), dim3(nblk), dim3(kBlock), 0, s, g, w, p, ybar, un, q,    \
+                           tb, tw, u0bar, mode, ubar_out, zc);                                                        \
+    } while (0)
         if (proj_u && has_w)
             INS_WVJP_ZM(true, true);
         else if (proj_u)
