@@ -770,9 +770,11 @@ void eddy_alloc(ins_ctx c) {
     closure_alloc_common(c);
 }
 
-// m = m_theta(u); leaves x0, z1, a1, z2, a2 for a following pullback.
+// m = m_theta(u); leaves x0, z1, a1, z2, a2 for a following pullback. Without
+// need_m the learned closure's output layer is left out: its own pullback reads a2
+// and the cotangent, not m.
 template <typename T>
-void closure_forward(ins_ctx c, const T* u, T* m, bool keep_z = true) {
+void closure_forward(ins_ctx c, const T* u, T* m, bool keep_z = true, bool need_m = true) {
     const ins::Grid& g = c->g;
     if (c->clos_kind == 2) {
         c->eddy_u = u;
@@ -791,6 +793,7 @@ void closure_forward(ins_ctx c, const T* u, T* m, bool keep_z = true) {
     c->launch("cnn_conv2", [&] {
         return ins::launch_closure_conv<T>(g, 1, c->a1, c->wf[1], c->theta + kB2, nullptr, z2, c->a2, nullptr, c->stream);
     });
+    if (!need_m) return;
     c->launch("cnn_conv3", [&] {
         return ins::launch_closure_conv<T>(g, 2, c->a2, c->wf[2], c->theta + kB3, nullptr, nullptr, nullptr, m, c->stream);
     });
@@ -832,7 +835,7 @@ void closure_backward(ins_ctx c, const T* mbar, T* ubar) {
 
 // Closure term at the stage velocity u_i = (p ? w - G p : w); returns m or nullptr.
 template <typename T>
-const T* closure_at_stage(ins_ctx c, const T* w, const double* p, bool keep_z = false) {
+const T* closure_at_stage(ins_ctx c, const T* w, const double* p, bool keep_z = false, bool need_m = true) {
     if (!c->clos_on) return nullptr;
     const T* u = w;
     if (p) {
@@ -841,7 +844,7 @@ const T* closure_at_stage(ins_ctx c, const T* w, const double* p, bool keep_z = 
         u = ui;
     }
     T* m = static_cast<T*>(c->mclos);
-    closure_forward<T>(c, u, m, keep_z);
+    closure_forward<T>(c, u, m, keep_z, need_m);
     return m;
 }
 
@@ -970,7 +973,7 @@ void stage_vjp(ins_ctx c, const T* w, const double* p, bool proj_u, const T* yba
     });
     if (c->clos_on) {
         // the closure's share of the stage pullback: m_bar = Fbar_i, at u_i
-        closure_at_stage<T>(c, w, proj_u ? p : nullptr, true);
+        closure_at_stage<T>(c, w, proj_u ? p : nullptr, true, false);
         closure_backward<T>(c, fb, mode >= 2 ? u0bar : out);
     }
 }
@@ -1455,7 +1458,7 @@ ins_status ins_rhs_vjp(ins_ctx ctx, const void* u, const void* fbar, void* ubar)
                                               static_cast<T*>(ubar), ctx->stream);
             });
             if (ctx->clos_on) {
-                closure_forward<T>(ctx, static_cast<const T*>(u), static_cast<T*>(ctx->mclos));
+                closure_forward<T>(ctx, static_cast<const T*>(u), static_cast<T*>(ctx->mclos), true, false);
                 closure_backward<T>(ctx, static_cast<const T*>(fbar), static_cast<T*>(ubar));
             }
         });
