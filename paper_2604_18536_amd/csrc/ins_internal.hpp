@@ -142,6 +142,22 @@ hipError_t launch_fft_x_inv(const Grid& g, const cd* spec, double* p, const FftP
 hipError_t launch_fft_strided(const Grid& g, cd* spec, const FftPlan& pl, const FftPlan& rev, int axis, int mode,
                               int lines, const SolveTab& st, hipStream_t s);
 
+// 2D periodic grids: stages and reverse stages fused with the x passes of the solves
+// around them (k_rows2d.hip states each contract). rows2d_ok: whether they take the
+// field.
+bool rows2d_ok(const Grid& g);
+template <typename T>
+hipError_t launch_rows_stage(const Grid& g, const FftPlan& X, const cd* post, const cd* spec_in, cd* spec_out, bool proj,
+                             const T* w, const T* base, const T* yin, T* yout, double cy, T* wout, double cw, double* pout,
+                             hipStream_t s);
+template <typename T>
+hipError_t launch_rows_project(const Grid& g, const FftPlan& X, const cd* post, const cd* spec_in, const T* w, T* u_out,
+                               double* pout, hipStream_t s);
+template <typename T>
+hipError_t launch_rows_vjp(const Grid& g, const FftPlan& X, const cd* post, const cd* spec_in, cd* spec_out, const T* w,
+                           const double* p, const T* ybar, const T* un, double cb, double cw, T* u0bar, int mode,
+                           T* ubar_out, T* yb_out, hipStream_t s);
+
 // All-float32 comparison mode (float32 velocity and pressure-point fields,
 // every operation in float32): divergence, gradient, projection and RK stage
 // (no closure term; 3D stages as the z-march).

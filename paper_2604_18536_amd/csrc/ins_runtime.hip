@@ -236,6 +236,7 @@ struct ins_ctx_s {
     ins::SolveTab st{};
 
     cd* spec = nullptr;
+    cd* spec2 = nullptr;  // second half spectrum of the fused 2D row kernels (null: they are not used)
     double* p = nullptr;
     void* ry = nullptr;
     void* wa = nullptr;
@@ -906,12 +907,134 @@ Stages<T> own_stages(ins_ctx c) {
     return {{static_cast<T*>(c->w2), static_cast<T*>(c->w3), static_cast<T*>(c->w4)}, {c->p2, c->p3, c->p4}};
 }
 
+// ----------------------------------------------------------------------------
+// 2D periodic grids: the same schedules with the stages fused with the x passes of
+// the solves around them (k_rows2d.hip); between two of those kernels only the y
+// solve is launched, in place on the spectrum the next one reads. The spectra
+// alternate: the kernel reads c->sp(i) and writes c->sp(i + 1).
+// ----------------------------------------------------------------------------
+bool rows2d(ins_ctx c) { return c->spec2 && !c->gen && !c->clos_on; }
+
+struct RowSpectra {
+    ins_ctx c;
+    int i = 0;  // spectrum that the next kernel reads
+    cd* in() const { return i ? c->spec2 : c->spec; }
+    cd* out() const { return i ? c->spec : c->spec2; }
+    // solve along y what the last kernel wrote; it is read next
+    void solve() {
+        i ^= 1;
+        c->launch("fft_y_solve", [&] {
+            return ins::launch_fft_strided(c->g, in(), c->py, c->py_rev, 1, 2, c->lnl_y, c->st, c->stream);
+        });
+    }
+};
+
+template <typename T>
+void rows_stage(ins_ctx c, RowSpectra& sp, bool proj, const T* w, const T* base, const T* yin, T* yout, double cy, T* wout,
+                double cw, double* pout = nullptr) {
+    c->launch(proj ? "rows_stage" : "rows_stage_first", [&] {
+        return ins::launch_rows_stage<T>(c->g, c->px, c->d_post, proj ? sp.in() : nullptr, sp.out(), proj, w, base, yin,
+                                         yout, cy, wout, cw, pout, c->stream);
+    });
+    sp.solve();
+}
+
+template <typename T>
+void rows_project(ins_ctx c, RowSpectra& sp, const T* w, T* out, double* pout = nullptr) {
+    c->launch("rows_project", [&] {
+        return ins::launch_rows_project<T>(c->g, c->px, c->d_post, sp.in(), w, out, pout, c->stream);
+    });
+}
+
+template <typename T>
+void rows_vjp(ins_ctx c, RowSpectra& sp, const T* w, const double* p, const T* ybar, const T* un, double cb, double cw,
+              T* u0bar, int mode, T* out, T* yb_out = nullptr) {
+    c->launch("rows_vjp", [&] {
+        return ins::launch_rows_vjp<T>(c->g, c->px, c->d_post, sp.in(), out ? sp.out() : nullptr, w, p, ybar, un, cb, cw,
+                                       u0bar, mode, out, yb_out, c->stream);
+    });
+    if (out) sp.solve();
+}
+
+// The solve of D vel, left in the spectrum that the next row kernel reads.
+template <typename T>
+void rows_divergence(ins_ctx c, RowSpectra& sp, const T* vel) {
+    c->launch("fft_x_fwd_div", [&] {
+        return ins::launch_fft_x_fwd<T>(c->g, vel, nullptr, sp.out(), c->px, c->d_post, c->lnl_x, c->stream);
+    });
+    sp.solve();
+}
+
+// u1 null: only the stage inputs of `keep` (the recomputation of a pullback).
+template <typename T>
+void rows_step_rk4(ins_ctx c, const T* u0, T* u1, double dt, const Stages<T>* keep) {
+    T* y = u1 ? static_cast<T*>(c->ry) : nullptr;
+    T* W2 = keep ? keep->w[0] : static_cast<T*>(c->wa);
+    T* W3 = keep ? keep->w[1] : static_cast<T*>(c->wb);
+    T* W4 = keep ? keep->w[2] : static_cast<T*>(c->wa);
+    RowSpectra sp{c};
+    rows_stage<T>(c, sp, false, u0, u0, nullptr, y, dt / 6.0, W2, dt / 2.0);
+    rows_stage<T>(c, sp, true, W2, u0, y, y, dt / 3.0, W3, dt / 2.0, keep ? keep->p[0] : nullptr);
+    rows_stage<T>(c, sp, true, W3, u0, y, y, dt / 3.0, W4, dt, keep ? keep->p[1] : nullptr);
+    if (!u1) {
+        rows_project<T>(c, sp, nullptr, nullptr, keep->p[2]);
+        return;
+    }
+    // the new sum goes to a register of its own (a block reads its neighbour's last row)
+    T* sum = static_cast<T*>(c->wb);
+    rows_stage<T>(c, sp, true, W4, nullptr, y, sum, dt / 6.0, nullptr, 0.0, keep ? keep->p[2] : nullptr);
+    rows_project<T>(c, sp, sum, u1);
+}
+
+template <typename T>
+void rows_step_wray3(ins_ctx c, const T* u0, T* u1, double dt, const Stages<T>* keep) {
+    T* yacc = static_cast<T*>(c->ry);
+    T* W2 = keep ? keep->w[0] : static_cast<T*>(c->wa);
+    T* W3 = keep ? keep->w[1] : static_cast<T*>(c->wb);
+    RowSpectra sp{c};
+    rows_stage<T>(c, sp, false, u0, u0, nullptr, yacc, dt / 4.0, W2, dt * 8.0 / 15.0);
+    rows_stage<T>(c, sp, true, W2, yacc, nullptr, nullptr, 0.0, W3, dt * 5.0 / 12.0, keep ? keep->p[0] : nullptr);
+    if (!u1) {
+        rows_project<T>(c, sp, nullptr, nullptr, keep->p[1]);
+        return;
+    }
+    T* sum = static_cast<T*>(c->wa);
+    rows_stage<T>(c, sp, true, W3, yacc, nullptr, nullptr, 0.0, sum, dt * 3.0 / 4.0, keep ? keep->p[1] : nullptr);
+    rows_project<T>(c, sp, sum, u1);
+}
+
+template <typename T>
+void rows_step_rk4_reverse(ins_ctx c, const T* u0, const Stages<T>& S, const T* u1bar, T* u0bar, double dt) {
+    T* YB = static_cast<T*>(c->ry);
+    T* UA = static_cast<T*>(c->wa);
+    T* UB = static_cast<T*>(c->wb);
+    RowSpectra sp{c};
+    rows_divergence<T>(c, sp, u1bar);
+    rows_vjp<T>(c, sp, S.w[2], S.p[2], nullptr, u1bar, dt / 6.0, 0.0, u0bar, 0, UA, YB);
+    rows_vjp<T>(c, sp, S.w[1], S.p[1], YB, UA, dt / 3.0, dt, u0bar, 1, UB);
+    rows_vjp<T>(c, sp, S.w[0], S.p[0], YB, UB, dt / 3.0, dt / 2.0, u0bar, 1, UA);
+    rows_vjp<T>(c, sp, u0, nullptr, YB, UA, dt / 6.0, dt / 2.0, u0bar, 2, nullptr);
+}
+
+template <typename T>
+void rows_step_wray3_reverse(ins_ctx c, const T* u0, const Stages<T>& S, const T* u1bar, T* u0bar, double dt) {
+    T* YB = static_cast<T*>(c->ry);
+    T* UA = static_cast<T*>(c->wa);
+    T* UB = static_cast<T*>(c->wb);
+    RowSpectra sp{c};
+    rows_divergence<T>(c, sp, u1bar);
+    rows_vjp<T>(c, sp, S.w[1], S.p[1], nullptr, u1bar, dt * 3.0 / 4.0, 0.0, nullptr, 0, UA, YB);
+    rows_vjp<T>(c, sp, S.w[0], S.p[0], UA, UA, 0.0, dt * 5.0 / 12.0, YB, 1, UB);
+    rows_vjp<T>(c, sp, u0, nullptr, YB, UB, dt / 4.0, dt * 8.0 / 15.0, u0bar, 3, nullptr);
+}
+
 // Classical RK4, projection after every stage (Sec. 2.6.2), low-storage
 // schedule: accumulator y, stage registers wa/wb, one pressure per stage.
 // With `keep` the stage registers and pressures are the given buffers (the
 // same work, their contents left for the pullback).
 template <typename T>
 void step_rk4(ins_ctx c, const T* u0, T* u1, double dt, const Stages<T>* keep = nullptr) {
+    if (rows2d(c)) return rows_step_rk4<T>(c, u0, u1, dt, keep);
     T* y = static_cast<T*>(c->ry);
     T* wa = static_cast<T*>(c->wa);
     T* wb = static_cast<T*>(c->wb);
@@ -985,6 +1108,7 @@ void stage_vjp(ins_ctx c, const T* w, const double* p, bool proj_u, const T* yba
 //   wbar_i = P ubar_i,  u0bar = ybar + sum_i wbar_i + ubar_1.
 template <typename T>
 void step_rk4_reverse(ins_ctx c, const T* u0, const Stages<T>& S, const T* u1bar, T* u0bar, double dt) {
+    if (rows2d(c)) return rows_step_rk4_reverse<T>(c, u0, S, u1bar, u0bar, dt);
     T* YB = static_cast<T*>(c->ry);
     T* UA = static_cast<T*>(c->wa);
     T* UB = static_cast<T*>(c->wb);
@@ -1005,6 +1129,10 @@ template <typename T>
 void step_rk4_vjp(ins_ctx c, const T* u0, const T* u1bar, T* u0bar, double dt) {
     ensure_vjp_storage(c);
     const Stages<T> S = own_stages<T>(c);
+    if (rows2d(c)) {
+        rows_step_rk4<T>(c, u0, nullptr, dt, &S);
+        return step_rk4_reverse<T>(c, u0, S, u1bar, u0bar, dt);
+    }
     stage<T>(c, u0, nullptr, false, u0, nullptr, false, 0.0, S.w[0], dt / 2.0);
     poisson(c, S.w[0], nullptr, S.p[0]);
     stage<T>(c, S.w[0], S.p[0], true, u0, nullptr, false, 0.0, S.w[1], dt / 2.0);
@@ -1023,6 +1151,7 @@ void step_rk4_vjp(ins_ctx c, const T* u0, const T* u1bar, T* u0bar, double dt) {
 // `keep`, W_2, W_3 and their pressures go to the given buffers.
 template <typename T>
 void step_wray3(ins_ctx c, const T* u0, T* u1, double dt, const Stages<T>* keep = nullptr) {
+    if (rows2d(c)) return rows_step_wray3<T>(c, u0, u1, dt, keep);
     T* yacc = static_cast<T*>(c->ry);
     T* wa = static_cast<T*>(c->wa);
     T* wb = static_cast<T*>(c->wb);
@@ -1047,6 +1176,7 @@ void step_wray3(ins_ctx c, const T* u0, T* u1, double dt, const Stages<T>* keep 
 //   wbar_2 = P ubar_2; u0bar = yaccbar + wbar_2 + J_F(u0)^T (dt/4 yaccbar + dt 8/15 wbar_2).
 template <typename T>
 void step_wray3_reverse(ins_ctx c, const T* u0, const Stages<T>& S, const T* u1bar, T* u0bar, double dt) {
+    if (rows2d(c)) return rows_step_wray3_reverse<T>(c, u0, S, u1bar, u0bar, dt);
     T* YB = static_cast<T*>(c->ry);
     T* UA = static_cast<T*>(c->wa);
     T* UB = static_cast<T*>(c->wb);
@@ -1067,6 +1197,10 @@ template <typename T>
 void step_wray3_vjp(ins_ctx c, const T* u0, const T* u1bar, T* u0bar, double dt) {
     ensure_vjp_storage(c);
     const Stages<T> S = own_stages<T>(c);
+    if (rows2d(c)) {
+        rows_step_wray3<T>(c, u0, nullptr, dt, &S);
+        return step_wray3_reverse<T>(c, u0, S, u1bar, u0bar, dt);
+    }
     T* YB = static_cast<T*>(c->ry);
     stage<T>(c, u0, nullptr, false, u0, YB, true, dt / 4.0, S.w[0], dt * 8.0 / 15.0, "wray_stage1");
     poisson(c, S.w[0], nullptr, S.p[0]);
@@ -1278,6 +1412,8 @@ ins_status ins_create(const ins_grid* grid, ins_bc bc, double nu, ins_dtype dtyp
         }
 
         setup_fft(c, rx, ry, rz, false);
+        if (dtype != INS_FP32_ALL && ins::rows2d_ok(g))
+            c->spec2 = static_cast<cd*>(c->alloc(size_t(g.batch) * g.ny * g.sx * sizeof(cd)));
         c->p = static_cast<double*>(c->alloc(c->scal_bytes()));
         c->ry = c->alloc(c->vel_bytes());
         c->wa = c->alloc(c->vel_bytes());
