@@ -221,6 +221,14 @@ hipError_t launch_stage_vjp_zm(const Grid& g, const T* w, const double* p, bool 
 template <typename T>
 hipError_t launch_eddy_forward(const Grid& g, const T* u, T* nu, T* m, double c2, hipStream_t s);
 template <typename T>
+hipError_t launch_eddy_viscosity(const Grid& g, const T* u, T* nu, double c2, hipStream_t s);
+// 3D stage (launch_stage_zm, with wprev launch_stage_zm_yw) with the eddy term of the
+// stage velocity added to F.
+template <typename T>
+hipError_t launch_eddy_stage_zm(const Grid& g, const T* w, const double* p, bool proj, const T* u0, T* y, bool yinit,
+                                double cy, T* wout, double cw, double c2, const T* wprev, double ry, double rw,
+                                hipStream_t s);
+template <typename T>
 hipError_t launch_eddy_backward(const Grid& g, const T* u, const T* nu, const T* mbar, T* P, T* ubar, double c2,
                                 hipStream_t s);
 

@@ -772,13 +772,19 @@ void eddy_alloc(ins_ctx c) {
 }
 
 // m = m_theta(u); leaves x0, z1, a1, z2, a2 for a following pullback. Without
-// need_m the learned closure's output layer is left out: its own pullback reads a2
-// and the cotangent, not m.
+// need_m the learned closure's output layer and the eddy term itself are left out: the
+// pullbacks read a2 or nu_t and the cotangent, not m.
 template <typename T>
 void closure_forward(ins_ctx c, const T* u, T* m, bool keep_z = true, bool need_m = true) {
     const ins::Grid& g = c->g;
     if (c->clos_kind == 2) {
         c->eddy_u = u;
+        if (!need_m) {
+            c->launch("eddy_viscosity", [&] {
+                return ins::launch_eddy_viscosity<T>(g, u, static_cast<T*>(c->eddy_nu), c->eddy_c2, c->stream);
+            });
+            return;
+        }
         c->launch("eddy_forward", [&] {
             return ins::launch_eddy_forward<T>(g, u, static_cast<T*>(c->eddy_nu), m, c->eddy_c2, c->stream);
         });
@@ -849,6 +855,18 @@ const T* closure_at_stage(ins_ctx c, const T* w, const double* p, bool keep_z = 
     return m;
 }
 
+// The stage with the eddy term in one launch (3D grids): whether it took it.
+template <typename T>
+bool eddy_stage(ins_ctx c, const T* w, const double* p, bool proj, const T* u0, T* y, bool yinit, double cy, T* wout,
+                double cw, const T* wprev) {
+    if (c->clos_kind != 2 || !c->clos_on || c->g.dim != 3) return false;
+    c->launch("eddy_stage", [&] {
+        return ins::launch_eddy_stage_zm<T>(c->g, w, p, proj, u0, y, yinit, cy, wout, cw, c->eddy_c2, wprev, 1.0 / 3.0,
+                                            2.0 / 3.0, c->stream);
+    });
+    return true;
+}
+
 template <typename T>
 // ymode: 0 reads the accumulator y, 1 starts it at u0, 2 forms it as
 // u0 + (wprev - u0)/3 + 2 (w - u0)/3 from the unprojected stage inputs (RK4's
@@ -863,6 +881,7 @@ void stage(ins_ctx c, const T* w, const double* p, bool proj, const T* u0, T* y,
     if (ymode == 2) {
         if (c->f32all() || c->gen || c->walls || c->g.dim != 3 || !proj || !y || !wout || !wprev)
             raise(INS_ERR_UNSUPPORTED, "accumulator from the stage inputs: periodic 3D projected stages only");
+        if (eddy_stage<T>(c, w, p, true, u0, y, false, cy, wout, cw, wprev)) return;
         const T* mc = closure_at_stage<T>(c, w, p);
         c->launch(name, [&] {
             return ins::launch_stage_zm_yw<T>(c->g, w, p, u0, wprev, 1.0 / 3.0, 2.0 / 3.0, y, cy, wout, cw, c->stream,
@@ -886,6 +905,7 @@ void stage(ins_ctx c, const T* w, const double* p, bool proj, const T* u0, T* y,
         c->launch(name, [&] { return ins::launch_wall_stage<T>(c->g, w, p, proj, u0, y, yinit, cy, wout, cw, c->stream); });
         return;
     }
+    if (eddy_stage<T>(c, w, p, proj, u0, y, yinit, cy, wout, cw, nullptr)) return;
     const T* mc = closure_at_stage<T>(c, w, proj ? p : nullptr);
     c->launch(name, [&] {
         return ins::launch_stage<T>(c->g, w, p, proj, u0, y, yinit, cy, wout, cw, c->stream, mc);
@@ -2029,7 +2049,7 @@ ins_status ins_eddy_backward(ins_ctx ctx, const void* u, const void* mbar, void*
                 return sizeof(T) == 8 ? ins::launch_fill_zero(reinterpret_cast<double*>(ubar), nv, ctx->stream)
                                       : ins::launch_fill_zero_f(reinterpret_cast<float*>(ubar), nv, ctx->stream);
             });
-            closure_forward<T>(ctx, static_cast<const T*>(u), static_cast<T*>(ctx->mclos));
+            closure_forward<T>(ctx, static_cast<const T*>(u), static_cast<T*>(ctx->mclos), true, false);
             closure_backward<T>(ctx, static_cast<const T*>(mbar), static_cast<T*>(ubar));
         });
     });

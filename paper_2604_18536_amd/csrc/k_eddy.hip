@@ -13,6 +13,7 @@
 // i.e. +sum_b delta_b (2 nu_t S_ab): the appendix's sub-grid stress with the
 // sign that makes it dissipate energy.
 #include "k_common.hpp"
+#include "k_zmarch.hpp"
 
 namespace ins {
 
@@ -128,6 +129,219 @@ __global__ __launch_bounds__(kBlock) void k_eddy_term(Grid g, const T* __restric
             acc += (t0 - t1) * g.ih[b];
         }
         m[boff + a * g.ncell + c0] = T(acc);
+    }
+}
+
+// RK stage with the eddy-viscosity term on 3D grids, one z-march: the stage velocity
+// u = w - G p (PROJ; float64 projection) is formed once per plane on the tile plus two
+// cells in an LDS ring, nu_t of plane z + 1 once on the tile plus one cell, and plane z
+// then takes F(u) + M(u) from LDS only. Streams (PT, YW) and update as in k_stage_zm:
+//   y = (yinit ? u0 : y, or with YW u0 + ry (wprev - u0) + rw (w - u0)) + cy (F + M),
+//   wout = u0 + cw (F + M), each where given.
+// The stress on the z edges below a plane and T_zz are carried from the plane before.
+// The projection, nu_t, M and stage kernels it replaces moved 1.3 GB per stage of
+// 4 x 128^3 float32 cells through memory (382 us), this one 0.57-0.67 GB (160-179 us,
+// 3.7 TB/s): about 230 float64 operations per cell (50 us at the card's rate) and two
+// barriers per plane at 16 waves per CU are not fully overlapped with the loads. A step
+// 2631 -> 1840 us, float64 at 128^3 982 -> 564 us.
+// All loads of the plane loop are unconditional, as in k_stage_zm.
+template <typename T, int HX, int HP>
+struct EddyRing {
+    const T *zm, *z0, *zp;  // ring slots of the planes below, at and above
+    int centre;
+    __device__ __forceinline__ double operator()(int c, int dx, int dy, int dz) const {
+        return double((dz < 0 ? zm : (dz > 0 ? zp : z0))[c * HP + centre + dy * HX + dx]);
+    }
+    __device__ __forceinline__ T operator()(int c, const Nb&, int dx, int dy, int dz) const {
+        return (dz < 0 ? zm : (dz > 0 ? zp : z0))[c * HP + centre + dy * HX + dx];
+    }
+};
+
+template <typename T, bool PROJ, int TX, int TY, bool YW, int PT>
+__global__ __launch_bounds__(TX * TY) void k_eddy_stage_zm(Grid g, const T* __restrict__ w, const double* __restrict__ p,
+                                                             const T* __restrict__ u0, T* __restrict__ y, int yinit, T cy,
+                                                             T* wout, T cw, int zc, double c2, const T* wprev, T ry, T rw) {
+    constexpr int NT = TX * TY, HX = TX + 4, HP = HX * (TY + 4), NX = TX + 2, NP = NX * (TY + 2), NR = 5;
+    constexpr int NS = (HP + NT - 1) / NT, NN = (NP + NT - 1) / NT;
+    constexpr bool LB = (PT & 1) != 0, LY = (PT & 2) != 0;
+    __shared__ T ring[NR][3 * HP];
+    __shared__ T nu[2][NP];
+    const int nx = g.nx, ny = g.ny, nz = g.nz;
+    const int ntx = (nx + TX - 1) / TX, nty = (ny + TY - 1) / TY, nzc = (nz + zc - 1) / zc;
+    int L = xcd_logical(blockIdx.x, gridDim.x);
+    const int tx = L % ntx;
+    L /= ntx;
+    const int ty = L % nty;
+    L /= nty;
+    const int zci = L % nzc;
+    const int b = L / nzc;
+    const int x0 = tx * TX, y0 = ty * TY, z0 = zci * zc;
+    const int z1 = min(z0 + zc, nz);
+    const int64_t boff = int64_t(b) * 3 * g.ncell;
+    const T* wb = w + boff;
+    const double* pb = PROJ ? p + int64_t(b) * g.ncell : nullptr;
+    const int nc = int(g.ncell);
+    const int plane = nx * ny;
+
+    // halo-plane positions loaded by this thread (slots past the halo load the
+    // first position and are not parked)
+    int hxy[NS], hxp[NS], hyp[NS];
+#pragma unroll
+    for (int s = 0; s < NS; ++s) {
+        const int q = threadIdx.x + s * NT;
+        const int qq = q < HP ? q : 0;
+        const int gx = pmod(x0 - 2 + qq % HX, nx);
+        const int gy = pmod(y0 - 2 + qq / HX, ny);
+        hxy[s] = gy * nx + gx;
+        hxp[s] = gy * nx + (gx + 1 == nx ? 0 : gx + 1);
+        hyp[s] = (gy + 1 == ny ? 0 : gy + 1) * nx + gx;
+    }
+    const int lx = threadIdx.x % TX, ly = threadIdx.x / TX;
+    const int cxg = x0 + lx, cyg = y0 + ly;
+    const bool valid = cxg < nx && cyg < ny;
+    const int cxy = min(cyg, ny - 1) * nx + min(cxg, nx - 1);
+    const int centre = (ly + 2) * HX + (lx + 2);
+    const int ncen = (ly + 1) * NX + (lx + 1);
+
+    T vw[NS][3];
+    double vp[NS][4];
+    auto fetch = [&](int zz) {
+        const int zoff = zz * plane;
+        const int zpo = (zz + 1 == nz ? 0 : zz + 1) * plane;
+#pragma unroll
+        for (int s = 0; s < NS; ++s) {
+            const int j = zoff + hxy[s];
+            vw[s][0] = wb[j];
+            vw[s][1] = wb[nc + j];
+            vw[s][2] = wb[2 * nc + j];
+            if constexpr (PROJ) {
+                vp[s][0] = pb[j];
+                vp[s][1] = pb[zoff + hxp[s]];
+                vp[s][2] = pb[zoff + hyp[s]];
+                vp[s][3] = pb[zpo + hxy[s]];
+            }
+        }
+    };
+    auto park = [&](T* slot) {
+#pragma unroll
+        for (int s = 0; s < NS; ++s) {
+            const int q = threadIdx.x + s * NT;
+            if (q < HP) {
+                if constexpr (PROJ) {
+                    const double pc = vp[s][0];
+                    slot[q] = T(double(vw[s][0]) - (vp[s][1] - pc) * g.ih[0]);
+                    slot[HP + q] = T(double(vw[s][1]) - (vp[s][2] - pc) * g.ih[1]);
+                    slot[2 * HP + q] = T(double(vw[s][2]) - (vp[s][3] - pc) * g.ih[2]);
+                } else {
+                    slot[q] = vw[s][0];
+                    slot[HP + q] = vw[s][1];
+                    slot[2 * HP + q] = vw[s][2];
+                }
+            }
+        }
+    };
+    auto viscosity = [&](const T* zm, const T* zc0, const T* zp, T* out) {
+#pragma unroll 1
+        for (int s = 0; s < NN; ++s) {
+            const int q = threadIdx.x + s * NT;
+            if (q < NP) {
+                const int qy = q / NX;
+                const EddyRing<T, HX, HP> U{zm, zc0, zp, (qy + 1) * HX + (q - qy * NX) + 1};
+                double S[3][3];
+                out[q] = T(c2 * centre_strain<3>(U, g, 0, 0, 0, S));
+            }
+        }
+    };
+    constexpr bool WPT = YW;
+    T pbase[3] = {T(0), T(0), T(0)}, pyv[3] = {T(0), T(0), T(0)}, pwc[3] = {T(0), T(0), T(0)};
+    const T* ysrc = YW ? wprev : y;
+    auto fetch_point = [&](int z) {
+        const int c0 = z * plane + cxy;
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            const int64_t kk = boff + int64_t(a) * nc + c0;
+            if constexpr (LB) pbase[a] = ld_stream(u0 + kk);
+            if constexpr (LY) pyv[a] = ld_stream(ysrc + kk);
+            if constexpr (WPT) pwc[a] = wb[int64_t(a) * nc + c0];
+        }
+    };
+
+    // planes z0 - 2 .. z0 + 1 parked, nu_t of z0 - 1; then plane z0 - 1 runs through the
+    // loop without output (the stresses it leaves are carried into z0)
+    T *s0 = ring[0], *s1 = ring[1], *s2 = ring[2], *s3 = ring[3], *s4 = ring[4];  // planes z - 1 .. z + 3
+#pragma unroll 1
+    for (int k = 0; k < 4; ++k) {
+        fetch(pmod(z0 - 2 + k, nz));
+        park(ring[k]);
+    }
+    T *n0 = nu[0], *n1 = nu[1];
+    __syncthreads();
+    viscosity(s0, s1, s2, n0);
+    double txz_m = 0.0, tyz_m = 0.0, tzz0 = 0.0;
+    for (int z = z0 - 1; z < z1; ++z) {
+        fetch(pmod(min(z + 3, z1 + 1), nz));
+        viscosity(s1, s2, s3, n1);
+        __syncthreads();  // nu_t of z + 1 is read below
+        const EddyRing<T, HX, HP> U{s0, s1, s2, centre};
+        auto N = [&](int dx, int dy, int dz) { return double((dz ? n1 : n0)[ncen + dy * NX + dx]); };
+        // 4 T_ab on the (a, b) edge I + o (the factors 2 nu_e and S_ab hold powers of two)
+        auto edge = [&](int a, int b2, int ox, int oy, int oz) {
+            const int ax = a == 0, ay = a == 1, az = a == 2;
+            const int bx = b2 == 0, by = b2 == 1, bz = b2 == 2;
+            const double gab = (U(a, ox + bx, oy + by, oz + bz) - U(a, ox, oy, oz)) * g.ih[b2];
+            const double gba = (U(b2, ox + ax, oy + ay, oz + az) - U(b2, ox, oy, oz)) * g.ih[a];
+            return (N(ox, oy, oz) + N(ox + ax, oy + ay, oz + az) + N(ox + bx, oy + by, oz + bz) +
+                    N(ox + ax + bx, oy + ay + by, oz + az + bz)) *
+                   (gab + gba);
+        };
+        // T_aa / 2 at the pressure point I + e_a or I
+        auto diag = [&](int a, int o) {
+            const int ax = a == 0, ay = a == 1, az = a == 2;
+            return N(o * ax, o * ay, o * az) * diag_at(U, g, a, o * ax, o * ay, o * az);
+        };
+        const double txz = edge(0, 2, 0, 0, 0), tyz = edge(1, 2, 0, 0, 0), tzz1 = diag(2, 1);
+        if (z >= z0) {
+            const double txy = edge(0, 1, 0, 0, 0);
+            double M[3];
+            M[0] = 2.0 * (diag(0, 1) - diag(0, 0)) * g.ih[0] + 0.25 * (txy - edge(0, 1, 0, -1, 0)) * g.ih[1] +
+                   0.25 * (txz - txz_m) * g.ih[2];
+            M[1] = 2.0 * (diag(1, 1) - diag(1, 0)) * g.ih[1] + 0.25 * (txy - edge(0, 1, -1, 0, 0)) * g.ih[0] +
+                   0.25 * (tyz - tyz_m) * g.ih[2];
+            M[2] = 2.0 * (tzz1 - tzz0) * g.ih[2] + 0.25 * (txz - edge(0, 2, -1, 0, 0)) * g.ih[0] +
+                   0.25 * (tyz - edge(1, 2, 0, -1, 0)) * g.ih[1];
+            T F[3];
+            rhs_cell<T, 3>(g, U, Nb{}, F);
+            if (valid) {
+                const int c0 = z * plane + cyg * nx + cxg;
+#pragma unroll
+                for (int a = 0; a < 3; ++a) {
+                    const int64_t kk = boff + int64_t(a) * nc + c0;
+                    const T base = LB ? pbase[a] : T(0);
+                    T yv;
+                    if constexpr (YW) yv = base + ry * (pyv[a] - base) + rw * (pwc[a] - base);
+                    else if constexpr (LY) yv = pyv[a];
+                    else yv = base;
+                    F[a] += T(M[a]);
+                    if (y) st_stream(yv + cy * F[a], y + kk);
+                    if (wout) st_stream(base + cw * F[a], wout + kk);
+                }
+            }
+        }
+        txz_m = txz;
+        tyz_m = tyz;
+        tzz0 = tzz1;
+        fetch_point(min(z + 1, z1 - 1));
+        park(s4);
+        T* sf = s0;
+        s0 = s1;
+        s1 = s2;
+        s2 = s3;
+        s3 = s4;
+        s4 = sf;
+        T* nf = n0;
+        n0 = n1;
+        n1 = nf;
+        __syncthreads();
     }
 }
 
@@ -274,6 +488,44 @@ hipError_t launch_eddy_backward(const Grid& g, const T* u, const T* nu, const T*
     return hipGetLastError();
 }
 
+template <typename T>
+hipError_t launch_eddy_viscosity(const Grid& g, const T* u, T* nu, double c2, hipStream_t s) {
+    INS_EDDY_DISPATCH(g, k_eddy_nu, g, u, nu, c2);
+    return hipGetLastError();
+}
+
+template <typename T>
+hipError_t launch_eddy_stage_zm(const Grid& g, const T* w, const double* p, bool proj, const T* u0, T* y, bool yinit,
+                                double cy, T* wout, double cw, double c2, const T* wprev, double ry, double rw,
+                                hipStream_t s) {
+    // 54 KB (64 x 8 float32) and 57 KB (32 x 8 float64) of LDS: two workgroups per CU and
+    // more; 64 x 8 in float64 would hold one.
+    constexpr int TX = sizeof(T) == 8 ? 32 : 64, TY = 8;
+    const int pt = ((wout || yinit) ? 1 : 0) | ((y && !yinit) ? 2 : 0);
+#define INS_ESZM(PR, YWI, PTI)                                                                                       \
+    do {                                                                                                             \
+        constexpr auto kern = &k_eddy_stage_zm<T, PR, TX, TY, YWI, PTI>;                                             \
+        const int zc = zm_chunk(g, TX, TY, resident_groups<kern, TX * TY>(), 64);                                    \
+        const int nblk = ((g.nx + TX - 1) / TX) * ((g.ny + TY - 1) / TY) * ((g.nz + zc - 1) / zc) * g.batch;         \
+        hipLaunchKernelGGL((k_eddy_stage_zm<T, PR, TX, TY, YWI, PTI>), dim3(nblk), dim3(TX * TY), 0, s, g, w, p, u0, \
+                           y, yinit ? 1 : 0, T(cy), wout, T(cw), zc, c2, wprev, T(ry), T(rw));                       \
+    } while (0)
+    if (wprev)
+        INS_ESZM(true, true, 3);
+    else if (!proj && pt == 3)
+        INS_ESZM(false, false, 3);
+    else if (!proj)
+        INS_ESZM(false, false, 1);
+    else if (pt == 3)
+        INS_ESZM(true, false, 3);
+    else if (pt == 2)
+        INS_ESZM(true, false, 2);
+    else
+        INS_ESZM(true, false, 1);
+#undef INS_ESZM
+    return hipGetLastError();
+}
+
 #undef INS_EDDY_DISPATCH
 
 template hipError_t launch_eddy_forward<double>(const Grid&, const double*, double*, double*, double, hipStream_t);
@@ -282,5 +534,13 @@ template hipError_t launch_eddy_backward<double>(const Grid&, const double*, con
                                                  double*, double, hipStream_t);
 template hipError_t launch_eddy_backward<float>(const Grid&, const float*, const float*, const float*, float*, float*,
                                                 double, hipStream_t);
+
+#define INS_EDDY_STAGE(T)                                                                                                \
+    template hipError_t launch_eddy_viscosity<T>(const Grid&, const T*, T*, double, hipStream_t);                        \
+    template hipError_t launch_eddy_stage_zm<T>(const Grid&, const T*, const double*, bool, const T*, T*, bool, double,  \
+                                                T*, double, double, const T*, double, double, hipStream_t);
+INS_EDDY_STAGE(double)
+INS_EDDY_STAGE(float)
+#undef INS_EDDY_STAGE
 
 }  // namespace ins

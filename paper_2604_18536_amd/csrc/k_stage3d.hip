@@ -30,22 +30,6 @@ struct LdsSrc {
     }
 };
 
-__device__ __forceinline__ int pmod(int v, int n) {
-    const int r = v % n;
-    return r < 0 ? r + n : r;
-}
-
-// Streams touched exactly once per step (u0, y, the new stage register) bypass
-// the caches' normal allocation.
-template <typename T>
-__device__ __forceinline__ T ld_stream(const T* p) {
-    return __builtin_nontemporal_load(p);
-}
-template <typename T>
-__device__ __forceinline__ void st_stream(T v, T* p) {
-    __builtin_nontemporal_store(v, p);
-}
-
 // P: type of the pressure and of the projection arithmetic w - G p (float64;
 // float32 only in the all-float32 comparison mode).
 // PT: the pointwise streams the stage reads at its own cells, fixed per

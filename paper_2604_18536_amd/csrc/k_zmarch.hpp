@@ -1,7 +1,7 @@
-// Work split of the z-marching 3D stencils (stages and reverse stages).
+// Work split and access helpers of the z-marching 3D stencils (stages and reverse stages).
 #pragma once
 
-#include "ins_internal.hpp"
+#include "k_common.hpp"
 
 namespace ins {
 
@@ -46,6 +46,22 @@ inline int zm_chunk(const Grid& g, int tx, int ty, int slots, int zmax) {
         }
     }
     return best;
+}
+
+__device__ __forceinline__ int pmod(int v, int n) {
+    const int r = v % n;
+    return r < 0 ? r + n : r;
+}
+
+// Streams touched exactly once per step (u0, y, the new stage register) bypass
+// the caches' normal allocation.
+template <typename T>
+__device__ __forceinline__ T ld_stream(const T* p) {
+    return __builtin_nontemporal_load(p);
+}
+template <typename T>
+__device__ __forceinline__ void st_stream(T v, T* p) {
+    __builtin_nontemporal_store(v, p);
 }
 
 }  // namespace ins
