@@ -24,6 +24,7 @@ namespace ins {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned short u16;
 
 constexpr int kTaps = 27;
@@ -34,17 +35,101 @@ __device__ __forceinline__ u16 bf16_bits(float v) {
 }
 __device__ __forceinline__ float bf16_val(u16 bits) { return float(__builtin_bit_cast(__bf16, bits)); }
 
-__device__ __forceinline__ float gelu_f(float z) { return 0.5f * z * (1.0f + erff(z * 0.70710678118654752f)); }
-__device__ __forceinline__ float gelu_grad_f(float z) {
-    return 0.5f * (1.0f + erff(z * 0.70710678118654752f)) + z * 0.39894228040143268f * expf(-0.5f * z * z);
+// Exact GELU z Phi(z) and its derivative Phi(z) + z phi(z) of N values per lane, after
+// erff and expf: two fits of their own (weighted least squares towards the minimax error).
+//   |z| < 1.4 (derivative: 1): z/2 + z^2 K(z^2) and 1/2 + z P(z^2), absolute error 2e-9;
+//   beyond, where any lane of the wave needs it: the upper tail
+//     Q(t) = 1 - Phi(t) = exp(-t^2/2) s (c1 + ... + c7 s^6),  s = 1 / (1 + 0.45 t),
+//   the form of Abramowitz & Stegun 7.1.26 (3e-9), and max(z, 0) - |z| Q(|z|), which does
+//   not cancel. Q is 0 beyond 20.
+// An epilogue evaluates one per output, 268 M at 4 x 128^3, on the same issue slots as
+// the matrix products: erff and expf were 60-70 % of the 8 -> 32 layers' vector work.
+// Those went from 398 (forward) and 520 us (pullback) to 364 and 423, the 32 -> 32 ones
+// from 705 and 800 to 660 and 734. Largest / rms error against float64 on [-7, 7]:
+// GELU 2.4e-7 / 5.5e-8 (erff 4.5e-7 / 7.3e-8), derivative 1.32e-7 / 2.72e-8 (1.42e-7 /
+// 2.74e-8); on a unit normal 2.4e-7 / 1.8e-8 (4.2e-7 / 2.5e-8) and 1.40e-7 / 2.59e-8
+// (1.43e-7 / 2.70e-8).
+constexpr float kGeluCentre = 1.4f, kGradCentre = 1.0f;
+
+// A constant in a scalar register: as literals half of the polynomials' constants were
+// moved to vector registers before each use.
+template <unsigned BITS>
+__device__ __forceinline__ float sconst() {
+    float r;
+    asm("s_mov_b32 %0, %1" : "=s"(r) : "i"(BITS));
+    return r;
+}
+#define INS_SC(v) sconst<__builtin_bit_cast(unsigned, v)>()
+
+template <int N>
+__device__ __forceinline__ bool gelu_far(const float (&z)[N], float centre) {
+    float m = 0.0f;
+#pragma unroll
+    for (int i = 0; i < N; ++i) m = fmaxf(m, fabsf(z[i]));
+    return __builtin_amdgcn_ballot_w64(m >= centre) != 0;
+}
+// e = exp(-z^2 / 2) and Q(min(|z|, 20)).
+__device__ __forceinline__ float gelu_tail(float z, float t, float& e) {
+    e = __builtin_amdgcn_exp2f(z * z * -0.72134752044448170f);
+    const float d = fmaf(t, INS_SC(0.45f), 1.0f);
+    float s = __builtin_amdgcn_rcpf(d);
+    s = fmaf(s, fmaf(-d, s, 1.0f), s);
+    float p = fmaf(s, INS_SC(-0.0377919599f), INS_SC(0.217211068f));
+    p = fmaf(s, p, INS_SC(-0.473691344f));
+    p = fmaf(s, p, INS_SC(0.39339155f));
+    p = fmaf(s, p, INS_SC(0.0182143468f));
+    p = fmaf(s, p, INS_SC(0.205396548f));
+    p = fmaf(s, p, INS_SC(0.177269787f));
+    return p * (s * e);
+}
+template <int N>
+__device__ __forceinline__ void gelu_n(const float (&z)[N], float (&a)[N]) {
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+        const float q = z[i] * z[i];
+        float k = fmaf(q, INS_SC(3.60695452e-07f), INS_SC(-8.32990918e-06f));
+        k = fmaf(q, k, INS_SC(0.000113203139f));
+        k = fmaf(q, k, INS_SC(-0.00118481647f));
+        k = fmaf(q, k, INS_SC(0.00997202843f));
+        k = fmaf(q, k, INS_SC(-0.0664899349f));
+        k = fmaf(q, k, INS_SC(0.398942232f));
+        a[i] = fmaf(q, k, 0.5f * z[i]);
+    }
+    if (gelu_far(z, kGeluCentre)) {
+#pragma unroll
+        for (int i = 0; i < N; ++i) {
+            float e;
+            const float t = fminf(fabsf(z[i]), 20.0f), tail = gelu_tail(z[i], t, e);
+            if (t >= kGeluCentre) a[i] = fmaf(z[i] > 0.0f ? -t : z[i], tail, fmaxf(z[i], 0.0f));
+        }
+    }
+}
+template <int N>
+__device__ __forceinline__ void gelu_grad_n(const float (&z)[N], float (&d)[N]) {
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+        const float q = z[i] * z[i];
+        float c = fmaf(q, INS_SC(-3.40459962e-07f), INS_SC(8.06192656e-06f));
+        c = fmaf(q, c, INS_SC(-0.000110526133f));
+        c = fmaf(q, c, INS_SC(0.00115069456f));
+        c = fmaf(q, c, INS_SC(-0.00949590001f));
+        c = fmaf(q, c, INS_SC(0.0598402545f));
+        c = fmaf(q, c, INS_SC(-0.265961319f));
+        c = fmaf(q, c, INS_SC(0.797884524f));
+        d[i] = fmaf(z[i], c, 0.5f);
+    }
+    if (gelu_far(z, kGradCentre)) {
+#pragma unroll
+        for (int i = 0; i < N; ++i) {
+            float e;
+            const float t = fminf(fabsf(z[i]), 20.0f), tail = gelu_tail(z[i], t, e);
+            const float far = fmaf(z[i] * 0.39894228040143268f, e, 0.5f + copysignf(0.5f - tail, z[i]));
+            if (t >= kGradCentre) d[i] = far;
+        }
+    }
 }
 
 __device__ __forceinline__ int wrapi(int v, int n) { return v < 0 ? v + n : (v >= n ? v - n : v); }
-__device__ __forceinline__ int pmod_i(int v, int n) {
-    const int r = v % n;
-    return r < 0 ? r + n : r;
-}
-
 // K tile kt, lane group gq: which tap and which first channel the lane's 8 operands hold.
 template <int CIN>
 __device__ __forceinline__ void ktile_tap(int kt, int gq, int& tap, int& c0) {
@@ -89,18 +174,38 @@ __device__ __forceinline__ int conv_row(int wave, int mt) { return (mt >> 1) * k
 
 // The convolution kernel's output block is 32 x 4 x BZ cells: BZ = 4 for the
 // 32-channel inputs (every weight operand a wave fetches then feeds 8 MFMAs
-// instead of 4), BZ = 2 for the 8-channel ones. Its epilogue stages 256 cells
-// (two planes) at a time.
+// instead of 4), BZ = 2 for the 8-channel ones.
+//
+// What bounds it at 4 x 128^3 (us, before -> now): two or three workgroups per CU (LDS)
+// run load, products and epilogue one after the other, so every serial wait counts. All
+// loads of the input block are in flight together (before: one round trip of 4 per
+// thread after the other), as are the z or cotangent values the epilogue reads (before:
+// round trips through LDS or one at a time after the products); the 3-channel outputs
+// are written as whole rows. 32 -> 32 676 -> 579 (464 GFLOP: 0.8 PFLOP/s) and pullback
+// 861 -> 666, 8 -> 32 401 -> 351 and pullback 705 -> 383, 32 -> 3 469 -> 356 and
+// pullback 537 -> 366. (The staging arrays are native vectors: as arrays of uint4 they
+// were kept in scratch memory and everything took 1.5-2 times as long.)
 template <int BZ>
 constexpr int conv_halo_cells() { return kChX * kChY * (BZ + 2); }
 
-// keep_z false: a forward-only hidden layer stages only its bfloat16 output
-// (the smaller footprint lets more workgroups share a CU).
+// Cells from one 8-channel chunk of the input block in LDS to the next: a multiple of
+// 16, all the banks, so that lanes of different chunks conflict only if their cells do.
 template <int CIN, int BZ>
-constexpr size_t conv_t_lds_bytes(bool keep_z = true) {
-    const size_t halo = size_t(conv_halo_cells<BZ>()) * CIN * 2;
-    const size_t epi = size_t(kCbCells) * 32 * (keep_z ? 4 + 2 : 2);  // float32 z (or zin) + bfloat16 out
+constexpr int conv_chunk_cells() { return CIN == 32 ? (conv_halo_cells<BZ>() + 15) / 16 * 16 : conv_halo_cells<BZ>(); }
+constexpr int kAtRow = 40;  // bfloat16 output cell in LDS: 32 channels padded (conflict-free stores)
+
+template <int CIN, int BZ>
+constexpr size_t conv_t_lds_bytes(bool hidden) {
+    const size_t halo = size_t(conv_chunk_cells<CIN, BZ>()) * CIN * 2;
+    const size_t epi = size_t(kCbX * kCbY * BZ) * (hidden ? kAtRow * 2 : 3 * 4);
     return halo > epi ? halo : epi;
+}
+
+// v in [-1, n + 4] into [0, n), n >= 2.
+__device__ __forceinline__ int wrap_near(int v, int n) {
+    v = v < 0 ? v + n : v;
+    v = v >= n ? v - n : v;
+    return v >= n ? v - n : v;
 }
 
 template <typename T, int CIN, int NT, int EPI, int BZ>
@@ -110,8 +215,9 @@ __global__ __launch_bounds__(kBlock) void k_conv_t(Grid g, const u16* __restrict
                                                      T* __restrict__ fout, int nout) {
     constexpr int NKT = (kTaps * CIN + 31) / 32;
     constexpr int MT = 2 * BZ;  // M tiles per wave: BZ planes x 2 halves of x
-    constexpr int HZ = BZ + 2, HCELLS = conv_halo_cells<BZ>();
+    constexpr int HZ = BZ + 2, HCELLS = conv_halo_cells<BZ>(), HC = conv_chunk_cells<CIN, BZ>();
     constexpr int CH = CIN / 8;  // 16-byte chunks per cell
+    constexpr int NROW = kChY * HZ;
     extern __shared__ __attribute__((aligned(16))) u16 xs[];
     const int nx = g.nx, ny = g.ny, nz = g.nz;
     const int nbx = nx / kCbX, nby = (ny + kCbY - 1) / kCbY, nbz = (nz + BZ - 1) / BZ;
@@ -125,22 +231,87 @@ __global__ __launch_bounds__(kBlock) void k_conv_t(Grid g, const u16* __restrict
     const int x0 = bx * kCbX, y0 = by * kCbY, z0 = bz * BZ;
     const int tid = threadIdx.x;
     const int64_t bcell = int64_t(b) * nz * ny * nx;
-    // 1. input block with periodic halo -> LDS
-    for (int cell = tid; cell < HCELLS; cell += kBlock) {
-        const int hx = cell % kChX, hy = (cell / kChX) % kChY, hz = cell / (kChX * kChY);
-        const int gx = wrapi(x0 - 1 + hx, nx);
-        const int gy = pmod_i(y0 - 1 + hy, ny), gz = pmod_i(z0 - 1 + hz, nz);
-        const int64_t gc = bcell + (int64_t(gz) * ny + gy) * nx + gx;
-        uint4 v[CH];
-#pragma unroll
-        for (int ch = 0; ch < CH; ++ch) v[ch] = *reinterpret_cast<const uint4*>(in + gc * CIN + ch * 8);
-#pragma unroll
-        for (int ch = 0; ch < CH; ++ch) *reinterpret_cast<uint4*>(xs + (ch * HCELLS + cell) * 8) = v[ch];
-    }
-    __syncthreads();
-    // 2. implicit GEMM from LDS
-    const int lane = tid & 63, wave = tid >> 6;
+    const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int lm = lane & 15, gq = lane >> 4;
+    // 1. input block with periodic halo -> LDS. A wave takes whole halo rows, 64 / CH cells a
+    // load with the lanes of a chunk together: the row's address is scalar and a lane's
+    // place in it the same for every row. The last two cells of every row follow. Every load of a
+    // thread is in flight before the first is stored.
+    auto row_base = [&](int row) {
+        const int hz = row / kChY, hy = row - hz * kChY;
+        return in + (bcell + int64_t(wrap_near(z0 - 1 + hz, nz) * ny + wrap_near(y0 - 1 + hy, ny)) * nx) * CIN;
+    };
+    constexpr int RW = CH == 4 ? 1 : 2, RPW = NROW / (4 * RW);  // rows a load covers, loads per 32 cells of a wave's rows
+    constexpr int NE = NROW * 2 * CH, KE = (NE + kBlock - 1) / kBlock;
+    static_assert(NROW % (4 * RW) == 0, "whole rows per wave");
+    const int sch = CH == 4 ? gq : 0, sx = CH == 4 ? lm : lane & 31, srow = CH == 4 ? 0 : lane >> 5;
+    u32x4 va[RPW], vb[RPW], ve[KE];
+    {
+        const int xo0 = wrapi(x0 - 1 + sx, nx) * CIN + sch * 8, xo1 = (x0 + 15 + sx) * CIN + sch * 8;
+#pragma unroll
+        for (int k = 0; k < RPW; ++k) {
+            const int row = (wave * RPW + k) * RW;
+            const u16* base = row_base(row);
+            if constexpr (RW == 2) {
+                const u16* next = row_base(row + 1);
+                base = srow ? next : base;
+            }
+            va[k] = *reinterpret_cast<const u32x4*>(base + xo0);
+            if constexpr (CH == 4) vb[k] = *reinterpret_cast<const u32x4*>(base + xo1);
+        }
+#pragma unroll
+        for (int k = 0; k < KE; ++k) {
+            const int e = min(k * kBlock + tid, NE - 1), row = e / (2 * CH);
+            ve[k] = *reinterpret_cast<const u32x4*>(row_base(row) + wrapi(x0 + 31 + (e / CH & 1), nx) * CIN + e % CH * 8);
+        }
+    }
+    // block cell q = r * 32 + x of block row r; its grid cell
+    auto block_cell = [&](int q, int64_t& c) -> bool {
+        const int r = q >> 5, xx = q & 31;
+        const int yy = y0 + r % kCbY, zz = z0 + r / kCbY;
+        c = bcell + (int64_t(zz) * ny + yy) * nx + x0 + xx;
+        return yy < ny && zz < nz;
+    };
+    // what the epilogue reads, in flight through the GEMM: z at this lane's accumulators,
+    // or the input cotangent so far at cell tid
+    constexpr int ZM = EPI == EPI_DGRAD_HIDDEN ? MT : 1;
+    float zr[ZM][4][NT];
+    T old[3];
+    if constexpr (EPI == EPI_DGRAD_HIDDEN) {
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt) {
+            const int r = conv_row(wave, mt);
+            const int yy = min(y0 + r % kCbY, ny - 1), zz = min(z0 + r / kCbY, nz - 1);
+            const float* zp = zin + (bcell + (int64_t(zz) * ny + yy) * nx + x0 + (mt & 1) * 16 + 4 * gq) * 32 + lm;
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+#pragma unroll
+                for (int nt = 0; nt < NT; ++nt) zr[mt][i][nt] = zp[i * 32 + nt * 16];
+        }
+    }
+    const int64_t vol = int64_t(nx) * ny * nz;
+    if constexpr (EPI == EPI_DGRAD_INPUT) {
+        int64_t c;
+        const bool ok = block_cell(tid, c);
+#pragma unroll
+        for (int n = 0; n < 3; ++n) old[n] = fout[(int64_t(b) * 3 + n) * vol + (ok ? c - bcell : 0)];
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    {
+        u16* dst = xs + (sch * HC + (wave * RPW * RW + srow) * kChX + sx) * 8;
+#pragma unroll
+        for (int k = 0; k < RPW; ++k) {
+            *reinterpret_cast<u32x4*>(dst + k * RW * kChX * 8) = va[k];
+            if constexpr (CH == 4) *reinterpret_cast<u32x4*>(dst + (k * RW * kChX + 16) * 8) = vb[k];
+        }
+#pragma unroll
+        for (int k = 0; k < KE; ++k) {
+            const int e = k * kBlock + tid;
+            if (e < NE)
+                *reinterpret_cast<u32x4*>(xs + (e % CH * HC + e / (2 * CH) * kChX + 32 + (e / CH & 1)) * 8) = ve[k];
+        }
+    }
+    // 2. implicit GEMM from LDS
     f32x4 acc[MT][NT];
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt)
@@ -154,18 +325,22 @@ __global__ __launch_bounds__(kBlock) void k_conv_t(Grid g, const u16* __restrict
         hbase[mt] = (zz * kChY + yy) * kChX + (mt & 1) * 16 + lm;
     }
     if constexpr (CIN == 32) {
-        const u16* xq = xs + (gq * HCELLS) * 8;  // this lane's 8-channel chunk
-        // the weight operands of tap column tyx (tz = 0, 1, 2), fetched one column ahead
-        bf16x8 bn[3][NT];
+        const u16* xq = xs + (gq * HC) * 8;  // this lane's 8-channel chunk
+        // the weight operands of tap column tyx (tz = 0, 1, 2), fetched PF columns ahead: a
+        // column is 12 BZ NT / 2 MFMAs of 16 cycles, an L2 access several hundred cycles
+        constexpr int PF = NT == 1 ? 9 : (BZ == 2 ? 2 : 1);
+        bf16x8 bn[PF][3][NT];
         auto fetch_w = [&](int tyx) {
 #pragma unroll
             for (int tz = 0; tz < 3; ++tz)
 #pragma unroll
                 for (int nt = 0; nt < NT; ++nt)
-                    bn[tz][nt] = *reinterpret_cast<const bf16x8*>(
+                    bn[tyx % PF][tz][nt] = *reinterpret_cast<const bf16x8*>(
                         wpk + (((tz * 9 + tyx) * NT * 16 + nt * 16 + lm) * 32 + 8 * gq));
         };
-        fetch_w(0);
+#pragma unroll
+        for (int k = 0; k < PF; ++k) fetch_w(k);
+        __syncthreads();
 #pragma unroll
         for (int tyx = 0; tyx < 9; ++tyx) {
             const int ty = tyx / 3, tx = tyx % 3;
@@ -173,8 +348,8 @@ __global__ __launch_bounds__(kBlock) void k_conv_t(Grid g, const u16* __restrict
 #pragma unroll
             for (int tz = 0; tz < 3; ++tz)
 #pragma unroll
-                for (int nt = 0; nt < NT; ++nt) bv[tz][nt] = bn[tz][nt];
-            if (tyx < 8) fetch_w(tyx + 1);
+                for (int nt = 0; nt < NT; ++nt) bv[tz][nt] = bn[tyx % PF][tz][nt];
+            if (tyx + PF < 9) fetch_w(tyx + PF);
             __builtin_amdgcn_sched_barrier(0);  // keep the prefetch ahead of this column's work
 #pragma unroll
             for (int hz = 0; hz < HZ; ++hz) {
@@ -204,6 +379,7 @@ __global__ __launch_bounds__(kBlock) void k_conv_t(Grid g, const u16* __restrict
             bn[nt] = *reinterpret_cast<const bf16x8*>(wpk + ((kt * NT * 16 + nt * 16 + lm) * 32 + 8 * gq));
     };
     fetch_w(0);
+    __syncthreads();
 #pragma unroll
     for (int kt = 0; kt < NKT; ++kt) {
         int tap, c0;
@@ -220,7 +396,7 @@ __global__ __launch_bounds__(kBlock) void k_conv_t(Grid g, const u16* __restrict
         for (int mt = 0; mt < MT; ++mt) {
             bf16x8 av;
             if (tap_ok) {
-                av = *reinterpret_cast<const bf16x8*>(xs + ((c0 >> 3) * HCELLS + hbase[mt] + toff) * 8);
+                av = *reinterpret_cast<const bf16x8*>(xs + (hbase[mt] + toff) * 8);
             } else {
 #pragma unroll
                 for (int j = 0; j < 8; ++j) av[j] = __bf16(0.0f);
@@ -233,93 +409,78 @@ __global__ __launch_bounds__(kBlock) void k_conv_t(Grid g, const u16* __restrict
     }
     // 3. epilogue: lane holds D[m = 4 gq + i][n = nt*16 + lm] of M tile mt, i.e. block
     // cell q = r * 32 + (mt & 1) * 16 + 4 gq + i with r = conv_row(wave, mt)
-    auto block_cell = [&](int q, int64_t& c) -> bool {
-        const int r = q >> 5, xx = q & 31;
-        const int yy = y0 + r % kCbY, zz = z0 + r / kCbY;
-        c = bcell + (int64_t(zz) * ny + yy) * nx + x0 + xx;
-        return yy < ny && zz < nz;
-    };
+    constexpr int NCELL = kCbX * kCbY * BZ;
+    __syncthreads();  // every wave is done reading the input block
     if constexpr (EPI == EPI_HIDDEN || EPI == EPI_DGRAD_HIDDEN) {
-        // per half of the block (planes 2h, 2h + 1: 256 cells, q = 256 h + local cell):
-        // [256][32] float32 z (not kept by a forward-only EPI_HIDDEN call: zout null),
-        // then [256][32] bfloat16
-        const bool keep_z = EPI == EPI_DGRAD_HIDDEN || zout != nullptr;
-        float* zt = reinterpret_cast<float*>(xs);
-        u16* at = keep_z ? reinterpret_cast<u16*>(xs + kCbCells * 32 * 2) : xs;
+        // z (if kept) from the registers, 64-byte runs; the bfloat16 output through LDS
+        u16* at = xs;
+        float bv[NT];
+        if constexpr (EPI == EPI_HIDDEN)
 #pragma unroll
-        for (int h = 0; h < BZ / 2; ++h) {
-            const int qh = h * kCbCells;
-            __syncthreads();  // every wave is done reading the input block / the previous half
-            if constexpr (EPI == EPI_DGRAD_HIDDEN) {
-                for (int e = tid; e < kCbCells * 8; e += kBlock) {  // zin block, 16-byte chunks
-                    const int q = e >> 3, ch = e & 7;
-                    int64_t c;
-                    float4 v = {0.f, 0.f, 0.f, 0.f};
-                    if (block_cell(qh + q, c)) v = *reinterpret_cast<const float4*>(zin + c * 32 + ch * 4);
-                    *reinterpret_cast<float4*>(zt + q * 32 + ch * 4) = v;
-                }
-                __syncthreads();
-            }
-#pragma unroll
-            for (int mt = 4 * h; mt < 4 * h + 4; ++mt) {
-                const int qb = conv_row(wave, mt) * 32 + (mt & 1) * 16 + 4 * gq - qh;
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const int q = qb + i;
-#pragma unroll
-                    for (int nt = 0; nt < NT; ++nt) {
-                        const int n = nt * 16 + lm;
-                        const float v = acc[mt][nt][i];
-                        if constexpr (EPI == EPI_HIDDEN) {
-                            const float z = v + bias[n];
-                            if (keep_z) zt[q * 32 + n] = z;
-                            at[q * 32 + n] = bf16_bits(gelu_f(z));
-                        } else {
-                            at[q * 32 + n] = bf16_bits(v * gelu_grad_f(zt[q * 32 + n]));
-                        }
-                    }
-                }
-            }
-            __syncthreads();
-            for (int e = tid; e < kCbCells * 4; e += kBlock) {  // bfloat16 out: 4 chunks per cell
-                const int q = e >> 2, ch = e & 3;
-                int64_t c;
-                if (block_cell(qh + q, c))
-                    *reinterpret_cast<uint4*>(aout + c * 32 + ch * 8) =
-                        *reinterpret_cast<const uint4*>(at + q * 32 + ch * 8);
-            }
-            if (EPI == EPI_HIDDEN && zout) {
-                for (int e = tid; e < kCbCells * 8; e += kBlock) {  // float32 z: 8 chunks per cell
-                    const int q = e >> 3, ch = e & 7;
-                    int64_t c;
-                    if (block_cell(qh + q, c))
-                        *reinterpret_cast<float4*>(zout + c * 32 + ch * 4) =
-                            *reinterpret_cast<const float4*>(zt + q * 32 + ch * 4);
-                }
-            }
-        }
-    } else {
-        const int64_t vol = int64_t(nx) * ny * nz;
+            for (int nt = 0; nt < NT; ++nt) bv[nt] = bias[nt * 16 + lm];
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt) {
-            const int qb = conv_row(wave, mt) * 32 + (mt & 1) * 16 + 4 * gq;
+            const int qb = conv_row(wave, mt) * 32 + (mt & 1) * 16 + 4 * gq;  // four cells of a row
+            int64_t c;
+            const bool ok = block_cell(qb, c);
+            float z[4 * NT], o[4 * NT];
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                int64_t c;
-                if (!block_cell(qb + i, c)) continue;
+            for (int i = 0; i < 4; ++i)
 #pragma unroll
                 for (int nt = 0; nt < NT; ++nt) {
-                    const int n = nt * 16 + lm;
-                    if (n < nout) {
-                        const int64_t r = c - int64_t(b) * vol;
-                        T* dst = fout + (int64_t(b) * 3 + n) * vol + r;
-                        const float v = acc[mt][nt][i];
-                        if constexpr (EPI == EPI_OUT)
-                            *dst = T(v + bias[n]);
-                        else
-                            *dst = T(double(*dst) + double(v));
-                    }
+                    if constexpr (EPI == EPI_HIDDEN) z[i * NT + nt] = acc[mt][nt][i] + bv[nt];
+                    else z[i * NT + nt] = zr[mt][i][nt];
                 }
+            if constexpr (EPI == EPI_HIDDEN) {
+                if (zout && ok) {
+                    float* zp = zout + c * 32 + lm;
+#pragma unroll
+                    for (int i = 0; i < 4; ++i)
+#pragma unroll
+                        for (int nt = 0; nt < NT; ++nt) zp[i * 32 + nt * 16] = z[i * NT + nt];
+                }
+                gelu_n(z, o);
+            } else {
+                gelu_grad_n(z, o);
+            }
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+#pragma unroll
+                for (int nt = 0; nt < NT; ++nt) {
+                    const float v = EPI == EPI_HIDDEN ? o[i * NT + nt] : acc[mt][nt][i] * o[i * NT + nt];
+                    at[(qb + i) * kAtRow + nt * 16 + lm] = bf16_bits(v);
+                }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int e = tid; e < NCELL * 4; e += kBlock) {  // 4 chunks per cell
+            const int q = e >> 2, ch = e & 3;
+            int64_t c;
+            if (block_cell(q, c))
+                *reinterpret_cast<uint4*>(aout + c * 32 + ch * 8) =
+                    *reinterpret_cast<const uint4*>(at + q * kAtRow + ch * 8);
+        }
+    } else {
+        static_assert(NCELL == kBlock, "one cell per thread");
+        float* ot = reinterpret_cast<float*>(xs);  // [3][cell]
+        if (lm < nout) {
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt) {
+                const int qb = conv_row(wave, mt) * 32 + (mt & 1) * 16 + 4 * gq;
+                *reinterpret_cast<f32x4*>(ot + lm * NCELL + qb) = acc[mt][0];
+            }
+        }
+        __syncthreads();
+        int64_t c;
+        if (block_cell(tid, c)) {
+#pragma unroll
+            for (int n = 0; n < 3; ++n) {
+                T* dst = fout + (int64_t(b) * 3 + n) * vol + (c - bcell);
+                const float v = ot[n * NCELL + tid];
+                if constexpr (EPI == EPI_OUT)
+                    *dst = T(v + bias[n]);
+                else
+                    *dst = T(double(old[n]) + double(v));
             }
         }
     }
@@ -386,33 +547,48 @@ __global__ void k_pack_weights(const float* __restrict__ w, int cin, int cout, i
     }
 }
 
-// Weight gradient on the same 32 x 4 x 2 cell blocks as k_conv_t:
+// Weight gradient on 32 x 4 x 2 cell blocks:
 // W'[n][tap][c] = sum_p g[p][n] x[p + off(tap)][c], bias'[n] = sum_p g[p][n].
 // A workgroup stages, transposed to channel-major in LDS, the cotangent g of
 // its block (gT[n][p]) and the input x of the block's halo (xT[c][z][y][x]);
-// the K dimension of each MFMA is 32 cells of one block row. Wave w owns the
-// taps w, w + 4, ...; for each block row it loads its A operands (g) once and
-// reuses them for all its taps. A tap's B operand starts dx cells into the
-// halo row, i.e. 0, 2 or 4 bytes past a 16-byte boundary: two aligned reads
-// and a byte-align select it. Cells outside the grid (partial blocks in y or
-// z) stage g = 0. Workgroups loop over a contiguous range of blocks and write
-// per-workgroup partial sums (reduced in order by k_wgrad_reduce).
-constexpr int kStage = 4;                 // staging items whose loads a thread issues together
+// the K dimension of each MFMA is 32 cells of one block row. The work of a row is
+// split in 18 units over the waves: a tap column (dz, dy) with its three dx, and one
+// half of the 32 channels (of x, or of g where x has 8). A unit reads its B operand
+// once, 16 + 4 bytes per lane: the three dx start 0, 2 or 4 bytes past a 16-byte
+// boundary, and a byte-align selects each. (With taps dealt out singly every tap read
+// 32 bytes per lane: 27 x 2 x 2 LDS reads per row.) The loads of the next block are in flight through a
+// block's products. Cells outside the grid (partial blocks in y or z) stage g = 0.
+// Workgroups loop over a contiguous range of blocks and write per-workgroup partial
+// sums (reduced in order by k_wgrad_reduce). At 4 x 128^3: 32 x 32 channels 858 -> 750 us
+// (0.6 PFLOP/s), 3 (as 8) x 32 739 -> 409, 32 x 3 462 -> 332; what is left is 2 waves per
+// SIMD sharing MFMA (27 %), transposing and selecting (32 %) and LDS (40 %, half of it
+// conflicts of the 16- and 4-byte reads).
 constexpr int kGtStride = kCbCells + 8;  // gT row: 256 cells + pad (conflict-free A reads)
 constexpr int kXtRow = 40;               // xT halo row: 34 cells padded to 40
 constexpr int kXtStride = kChZ * kChY * kXtRow + 8;
 
+// LDS row of channel 8 ch + i, and the channel of a row. With 32 channels a wave stores
+// 4 chunks of 16 cell pairs at once; 4 rows between the chunks are 16 banks (the strides
+// are 4 times an odd number of dwords), so its stores do not conflict (chunk after chunk
+// they did, 8 cycles a store).
+template <int C>
+__device__ __forceinline__ constexpr int chan_row(int ch, int i) { return C == 32 ? (i & 3) + 4 * ch + 16 * (i >> 2) : i; }
+template <int C>
+__device__ __forceinline__ constexpr int row_chan(int r) { return C == 32 ? 8 * ((r >> 2) & 3) + (r & 3) + 4 * (r >> 4) : r; }
+
 template <int CIN, int COUTP>
-__global__ __launch_bounds__(kBlock) void k_wgrad_t(Grid g, const u16* __restrict__ gin, const u16* __restrict__ xin,
-                                                      float* __restrict__ partial) {
-    constexpr int MT = COUTP == 32 ? 2 : 1;  // tiles of output channels n
-    constexpr int NT = CIN == 32 ? 2 : 1;    // tiles of input channels c
-    constexpr int NTAP = 7;                  // taps per wave (27 over 4 waves)
+__global__ __launch_bounds__(kBlock, 2) void k_wgrad_t(Grid g, const u16* __restrict__ gin, const u16* __restrict__ xin,
+                                                         float* __restrict__ partial) {
+    constexpr int MT = COUTP == 32 ? 2 : 1;      // tiles of output channels n
+    constexpr int NT = CIN == 32 ? 2 : 1;        // tiles of input channels c
+    constexpr int MU = CIN == 32 ? MT : 1;       // tiles of n in a unit
+    constexpr int NU = 5;                        // units per wave (18 over 4 waves)
+    constexpr int NCOL = 9;
     extern __shared__ __attribute__((aligned(16))) u16 ws[];
     u16* gT = ws;                                // [MT*16][kGtStride]
     u16* xT = ws + MT * 16 * kGtStride;          // [NT*16][kXtStride]
     const int tid = threadIdx.x;
-    const int lane = tid & 63, wave = tid >> 6;
+    const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int lm = lane & 15, gq = lane >> 4;
     const int nx = g.nx, ny = g.ny, nz = g.nz;
     // padding channels stay zero
@@ -420,13 +596,13 @@ __global__ __launch_bounds__(kBlock) void k_wgrad_t(Grid g, const u16* __restric
         for (int e = tid; e < (MT * 16 - COUTP) * kGtStride; e += kBlock) gT[COUTP * kGtStride + e] = 0;
     if constexpr (NT * 16 > CIN)
         for (int e = tid; e < (NT * 16 - CIN) * kXtStride; e += kBlock) xT[CIN * kXtStride + e] = 0;
-    f32x4 acc[NTAP][MT][NT];
+    f32x4 acc[NU][3][MU];
 #pragma unroll
-    for (int j = 0; j < NTAP; ++j)
+    for (int j = 0; j < NU; ++j)
 #pragma unroll
-        for (int mt = 0; mt < MT; ++mt)
+        for (int dx = 0; dx < 3; ++dx)
 #pragma unroll
-            for (int nt = 0; nt < NT; ++nt) acc[j][mt][nt] = f32x4{0.f, 0.f, 0.f, 0.f};
+            for (int mt = 0; mt < MU; ++mt) acc[j][dx][mt] = f32x4{0.f, 0.f, 0.f, 0.f};
     float bacc = 0.f;
     const int nbx = nx / kCbX, nby = (ny + kCbY - 1) / kCbY, nbz = (nz + kCbZ - 1) / kCbZ;
     const int nblocks = nbx * nby * nbz * g.batch;
@@ -434,7 +610,11 @@ __global__ __launch_bounds__(kBlock) void k_wgrad_t(Grid g, const u16* __restric
     // blocks share two of their four halo planes, which are still in cache
     const int per = (nblocks + gridDim.x - 1) / gridDim.x;
     const int blk0 = blockIdx.x * per, blk1 = min(nblocks, blk0 + per);
-    for (int blk = blk0; blk < blk1; ++blk) {
+    // items of 8 channels of a cell pair along x: g of the block, x of the halo block
+    constexpr int G8 = COUTP / 8, NG = (kCbCells / 2) * G8, KG = (NG + kBlock - 1) / kBlock;
+    constexpr int C8 = CIN / 8, NX = kChZ * kChY * (kChX / 2) * C8, KX = (NX + kBlock - 1) / kBlock;
+    u32x4 g0[KG], g1[KG], h0[KX], h1[KX];
+    auto fetch = [&](int blk) {
         int L = blk;
         const int bz = L % nbz;
         L /= nbz;
@@ -444,78 +624,65 @@ __global__ __launch_bounds__(kBlock) void k_wgrad_t(Grid g, const u16* __restric
         const int b = L / nby;
         const int x0 = bx * kCbX, y0 = by * kCbY, z0 = bz * kCbZ;
         const int64_t bcell = int64_t(b) * nz * ny * nx;
-        __syncthreads();  // the previous block's operands are no longer read
-        // g of the block, cell pairs along x: gT[n][q], q = row * 32 + x; the loads of
-        // kStage items are issued before any is unpacked into LDS
-        constexpr int G8 = COUTP / 8;
-        constexpr int NG = (kCbCells / 2) * G8;
-        for (int e0 = 0; e0 < NG; e0 += kStage * kBlock) {
-            uint4 v0[kStage], v1[kStage];
 #pragma unroll
-            for (int k = 0; k < kStage; ++k) {
-                const int e = e0 + k * kBlock + tid;
-                const int ch = e % G8, pr = e / G8;
-                const int q = 2 * pr, r = q >> 5, xx = q & 31;
-                const int yy = y0 + r % kCbY, zz = z0 + r / kCbY;
-                v0[k] = uint4{0u, 0u, 0u, 0u};
-                v1[k] = uint4{0u, 0u, 0u, 0u};
-                if (e < NG && yy < ny && zz < nz) {
-                    const int64_t c = bcell + (int64_t(zz) * ny + yy) * nx + x0 + xx;
-                    v0[k] = *reinterpret_cast<const uint4*>(gin + c * COUTP + ch * 8);
-                    v1[k] = *reinterpret_cast<const uint4*>(gin + (c + 1) * COUTP + ch * 8);
-                }
-            }
-#pragma unroll
-            for (int k = 0; k < kStage; ++k) {
-                const int e = e0 + k * kBlock + tid;
-                if (e >= NG) continue;
-                const int ch = e % G8, q = 2 * (e / G8);
-                const unsigned a[4] = {v0[k].x, v0[k].y, v0[k].z, v0[k].w};
-                const unsigned bb[4] = {v1[k].x, v1[k].y, v1[k].z, v1[k].w};
-#pragma unroll
-                for (int i = 0; i < 8; ++i) {
-                    const unsigned lo = (a[i >> 1] >> ((i & 1) * 16)) & 0xffffu;
-                    const unsigned hi = (bb[i >> 1] >> ((i & 1) * 16)) & 0xffffu;
-                    *reinterpret_cast<unsigned*>(gT + (ch * 8 + i) * kGtStride + q) = lo | (hi << 16);
-                }
-            }
+        for (int k = 0; k < KG; ++k) {
+            const int e = min(k * kBlock + tid, NG - 1);
+            const int ch = e % G8, q = 2 * (e / G8), r = q >> 5;
+            const int yy = y0 + r % kCbY, zz = z0 + r / kCbY;
+            const bool ok = yy < ny && zz < nz;
+            const u16* src = gin + (bcell + (int64_t(ok ? zz : z0) * ny + (ok ? yy : y0)) * nx + x0 + (q & 31)) * COUTP + ch * 8;
+            g0[k] = *reinterpret_cast<const u32x4*>(src);
+            g1[k] = *reinterpret_cast<const u32x4*>(src + COUTP);
+            if (!ok) g0[k] = g1[k] = u32x4{0u, 0u, 0u, 0u};
         }
-        // x of the halo block, cell pairs along x: xT[c][(hz * 6 + hy) * 40 + hx]
-        constexpr int C8 = CIN / 8;
-        constexpr int NPAIR = kChZ * kChY * (kChX / 2);
-        constexpr int NX = NPAIR * C8;
-        for (int e0 = 0; e0 < NX; e0 += kStage * kBlock) {
-            uint4 v0[kStage], v1[kStage];
 #pragma unroll
-            for (int k = 0; k < kStage; ++k) {
-                const int e = min(e0 + k * kBlock + tid, NX - 1);
-                const int ch = e % C8, pr = e / C8;
-                const int hx = 2 * (pr % (kChX / 2)), hrow = pr / (kChX / 2);
-                const int hy = hrow % kChY, hz = hrow / kChY;
-                const int gy = pmod_i(y0 - 1 + hy, ny), gz = pmod_i(z0 - 1 + hz, nz);
-                const int64_t rowc = bcell + (int64_t(gz) * ny + gy) * nx;
-                const int gx0 = wrapi(x0 - 1 + hx, nx), gx1 = wrapi(x0 + hx, nx);
-                v0[k] = *reinterpret_cast<const uint4*>(xin + (rowc + gx0) * CIN + ch * 8);
-                v1[k] = *reinterpret_cast<const uint4*>(xin + (rowc + gx1) * CIN + ch * 8);
-            }
+        for (int k = 0; k < KX; ++k) {
+            const int e = min(k * kBlock + tid, NX - 1);
+            const int ch = e % C8, pr = e / C8;
+            const int hrow = pr / (kChX / 2), hx = 2 * (pr - hrow * (kChX / 2));
+            const int hz = hrow / kChY, hy = hrow - hz * kChY;
+            const int64_t rowc = bcell + (int64_t(wrap_near(z0 - 1 + hz, nz)) * ny + wrap_near(y0 - 1 + hy, ny)) * nx;
+            h0[k] = *reinterpret_cast<const u32x4*>(xin + (rowc + wrapi(x0 - 1 + hx, nx)) * CIN + ch * 8);
+            h1[k] = *reinterpret_cast<const u32x4*>(xin + (rowc + wrapi(x0 + hx, nx)) * CIN + ch * 8);
+        }
+    };
+    // 8 channels of a cell pair -> 8 rows of dst, one 32-bit store each
+    auto spread = [&](auto chans, const u32x4& lo, const u32x4& hi, u16* dst, int stride) {
+        constexpr int C = decltype(chans)::value;
+        const unsigned a[4] = {lo.x, lo.y, lo.z, lo.w}, c[4] = {hi.x, hi.y, hi.z, hi.w};
 #pragma unroll
-            for (int k = 0; k < kStage; ++k) {
-                const int e = e0 + k * kBlock + tid;
-                if (e >= NX) continue;
-                const int ch = e % C8, pr = e / C8;
-                const int hx = 2 * (pr % (kChX / 2)), hrow = pr / (kChX / 2);
-                const unsigned a[4] = {v0[k].x, v0[k].y, v0[k].z, v0[k].w};
-                const unsigned bb[4] = {v1[k].x, v1[k].y, v1[k].z, v1[k].w};
+        for (int i = 0; i < 4; ++i) {
+            *reinterpret_cast<unsigned*>(dst + chan_row<C>(0, 2 * i) * stride) = __builtin_amdgcn_perm(c[i], a[i], 0x05040100u);
+            *reinterpret_cast<unsigned*>(dst + chan_row<C>(0, 2 * i + 1) * stride) = __builtin_amdgcn_perm(c[i], a[i], 0x07060302u);
+        }
+    };
+    // offsets of this wave's units in xT (B operand) and gT (A operand)
+    int xo[NU], go[NU];
 #pragma unroll
-                for (int i = 0; i < 8; ++i) {
-                    const unsigned lo = (a[i >> 1] >> ((i & 1) * 16)) & 0xffffu;
-                    const unsigned hi = (bb[i >> 1] >> ((i & 1) * 16)) & 0xffffu;
-                    *reinterpret_cast<unsigned*>(xT + (ch * 8 + i) * kXtStride + hrow * kXtRow + hx) = lo | (hi << 16);
-                }
-            }
+    for (int j = 0; j < NU; ++j) {
+        const int u = min(wave + 4 * j, 2 * NCOL - 1), half = u / NCOL, col = u - half * NCOL;
+        xo[j] = ((col / 3) * kChY + col % 3) * kXtRow + (CIN == 32 ? half * 16 * kXtStride : 0);
+        go[j] = CIN == 32 ? 0 : half * 16 * kGtStride;
+    }
+    if (blk0 < blk1) fetch(blk0);
+    for (int blk = blk0; blk < blk1; ++blk) {
+        __syncthreads();  // the previous block's operands are no longer read
+#pragma unroll
+        for (int k = 0; k < KG; ++k) {
+            const int e = k * kBlock + tid;
+            if (e < NG) spread(std::integral_constant<int, COUTP>{}, g0[k], g1[k], gT + (e % G8) * 4 * kGtStride + 2 * (e / G8), kGtStride);
+        }
+#pragma unroll
+        for (int k = 0; k < KX; ++k) {
+            const int e = k * kBlock + tid;
+            const int pr = e / C8, hrow = pr / (kChX / 2);
+            if (e < NX)
+                spread(std::integral_constant<int, CIN>{}, h0[k], h1[k],
+                       xT + (e % C8) * 4 * kXtStride + hrow * kXtRow + 2 * (pr - hrow * (kChX / 2)), kXtStride);
         }
         __syncthreads();
-        // bias: thread (n = tid mod 32, part = tid / 32) sums cells part*32 .. +31 of channel n
+        fetch(min(blk + 1, blk1 - 1));
+        // bias: thread (row tid mod 32, part = tid / 32) sums cells part*32 .. +31 of its channel
         if ((tid & 31) < COUTP) {
             const u16* row = gT + (tid & 31) * kGtStride + (tid >> 5) * 32;
 #pragma unroll
@@ -529,32 +696,28 @@ __global__ __launch_bounds__(kBlock) void k_wgrad_t(Grid g, const u16* __restric
 #pragma unroll 1
         for (int r = 0; r < kCbY * kCbZ; ++r) {
             const int yy = r % kCbY, zz = r / kCbY;
-            bf16x8 av[MT];
+            const u16* gr = gT + lm * kGtStride + r * 32 + 8 * gq;
+            const u16* xr = xT + lm * kXtStride + (zz * kChY + yy) * kXtRow + 8 * gq;
+            bf16x8 av[MU];
+            if constexpr (CIN == 32)
 #pragma unroll
-            for (int mt = 0; mt < MT; ++mt)
-                av[mt] = *reinterpret_cast<const bf16x8*>(gT + (mt * 16 + lm) * kGtStride + r * 32 + 8 * gq);
+                for (int mt = 0; mt < MU; ++mt) av[mt] = *reinterpret_cast<const bf16x8*>(gr + mt * 16 * kGtStride);
 #pragma unroll
-            for (int j = 0; j < NTAP; ++j) {
-                const int tap = wave + 4 * j;
-                if (tap >= kTaps) continue;
-                const int dz = tap / 9, dy = (tap / 3) % 3, dx = tap % 3;
-                const int off = ((zz + dz) * kChY + (yy + dy)) * kXtRow + 8 * gq;
-                const unsigned bs = 2u * unsigned(dx & 1);  // byte shift within a dword
-                const bool wsh = dx == 2;                    // whole-dword shift
+            for (int j = 0; j < NU; ++j) {
+                if (wave + 4 * j >= 2 * NCOL) continue;
+                if constexpr (CIN != 32) av[0] = *reinterpret_cast<const bf16x8*>(gr + go[j]);
+                const uint4 c = *reinterpret_cast<const uint4*>(xr + xo[j]);
+                const unsigned d[5] = {c.x, c.y, c.z, c.w, *reinterpret_cast<const unsigned*>(xr + xo[j] + 8)};
 #pragma unroll
-                for (int nt = 0; nt < NT; ++nt) {
-                    const u16* rowp = xT + (nt * 16 + lm) * kXtStride + off;
-                    const uint4 c0 = *reinterpret_cast<const uint4*>(rowp);
-                    const uint4 c1 = *reinterpret_cast<const uint4*>(rowp + 8);
-                    const unsigned d[5] = {wsh ? c0.y : c0.x, wsh ? c0.z : c0.y, wsh ? c0.w : c0.z,
-                                           wsh ? c1.x : c0.w, wsh ? c1.y : c1.x};
+                for (int dx = 0; dx < 3; ++dx) {
                     unsigned o[4];
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) o[i] = __builtin_amdgcn_alignbyte(d[i + 1], d[i], bs);
+                    for (int i = 0; i < 4; ++i)
+                        o[i] = dx == 1 ? __builtin_amdgcn_alignbyte(d[i + 1], d[i], 2u) : d[i + dx / 2];
                     const bf16x8 bv = __builtin_bit_cast(bf16x8, (uint4{o[0], o[1], o[2], o[3]}));
 #pragma unroll
-                    for (int mt = 0; mt < MT; ++mt)
-                        acc[j][mt][nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av[mt], bv, acc[j][mt][nt], 0, 0, 0);
+                    for (int mt = 0; mt < MU; ++mt)
+                        acc[j][dx][mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av[mt], bv, acc[j][dx][mt], 0, 0, 0);
                 }
             }
         }
@@ -562,17 +725,18 @@ __global__ __launch_bounds__(kBlock) void k_wgrad_t(Grid g, const u16* __restric
     // partial layout per workgroup: [n (COUTP)][tap][c (CIN)] then bias [COUTP]
     float* out = partial + int64_t(blockIdx.x) * (COUTP * kTaps * CIN + COUTP);
 #pragma unroll
-    for (int j = 0; j < NTAP; ++j) {
-        const int tap = wave + 4 * j;
-        if (tap >= kTaps) continue;
+    for (int j = 0; j < NU; ++j) {
+        const int u = wave + 4 * j, half = u / NCOL, col = u - half * NCOL;
+        if (u >= 2 * NCOL) continue;
 #pragma unroll
-        for (int mt = 0; mt < MT; ++mt)
+        for (int dx = 0; dx < 3; ++dx)
 #pragma unroll
-            for (int nt = 0; nt < NT; ++nt)
+            for (int mt = 0; mt < MU; ++mt)
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
-                    const int n = mt * 16 + 4 * gq + i, c = nt * 16 + lm;
-                    if (n < COUTP && c < CIN) out[(n * kTaps + tap) * CIN + c] = acc[j][mt][nt][i];
+                    const int n = (CIN == 32 ? mt : half) * 16 + 4 * gq + i, c = (CIN == 32 ? half : 0) * 16 + lm;
+                    if (n < COUTP && c < CIN)
+                        out[(row_chan<COUTP>(n) * kTaps + col * 3 + dx) * CIN + row_chan<CIN>(c)] = acc[j][dx][mt][i];
                 }
     }
     // the eight partial bias sums of each channel, added in part order
@@ -584,7 +748,7 @@ __global__ __launch_bounds__(kBlock) void k_wgrad_t(Grid g, const u16* __restric
         float sum = 0.f;
 #pragma unroll
         for (int part = 0; part < kBlock / 32; ++part) sum += red[part * 32 + tid];
-        out[COUTP * kTaps * CIN + tid] = sum;
+        out[COUTP * kTaps * CIN + row_chan<COUTP>(tid)] = sum;
     }
 }
 
@@ -655,7 +819,7 @@ hipError_t launch_closure_conv(const Grid& g, int which, const u16* in, const u1
     do {                                                                                                            \
         constexpr int BZ = CIN == 32 && EPI == EPI_HIDDEN ? 4 : 2;                                                  \
         const int grid = (g.nx / kCbX) * ((g.ny + kCbY - 1) / kCbY) * ((g.nz + BZ - 1) / BZ) * g.batch;            \
-        const size_t shm = conv_t_lds_bytes<CIN, BZ>(EPI != EPI_HIDDEN || zout != nullptr);                         \
+        const size_t shm = conv_t_lds_bytes<CIN, BZ>(EPI == EPI_HIDDEN || EPI == EPI_DGRAD_HIDDEN);                         \
         hipLaunchKernelGGL((k_conv_t<T, CIN, NT, EPI, BZ>), dim3(grid), dim3(kBlock), shm, s, g, in, wpk, bias, zin, \
                            zout, aout, fout, NOUT);                                                                 \
     } while (0)
