@@ -172,9 +172,9 @@ constexpr int kChX = kCbX + 2, kChY = kCbY + 2, kChZ = kCbZ + 2, kChCells = kChX
 // Block row (y + 4 z) of M tile mt of wave w: row y = w of plane mt / 2.
 __device__ __forceinline__ int conv_row(int wave, int mt) { return (mt >> 1) * kCbY + wave; }
 
-// The convolution kernel's output block is 32 x 4 x BZ cells: BZ = 4 for the
-// 32-channel inputs (every weight operand a wave fetches then feeds 8 MFMAs
-// instead of 4), BZ = 2 for the 8-channel ones.
+// The convolution kernel's output block is 32 x 4 x BZ cells: BZ = 4 for 32 -> 32
+// channels (every weight operand a wave fetches then feeds 8 MFMAs instead of 4: 579 us
+// against 675 with BZ = 2, pullback 647 against 667), else 2.
 //
 // What bounds it at 4 x 128^3 (us, before -> now): two or three workgroups per CU (LDS)
 // run load, products and epilogue one after the other, so every serial wait counts. All
@@ -182,8 +182,8 @@ __device__ __forceinline__ int conv_row(int wave, int mt) { return (mt >> 1) * k
 // thread after the other), as are the z or cotangent values the epilogue reads (before:
 // round trips through LDS or one at a time after the products); the 3-channel outputs
 // are written as whole rows. 32 -> 32 676 -> 579 (464 GFLOP: 0.8 PFLOP/s) and pullback
-// 861 -> 666, 8 -> 32 401 -> 351 and pullback 705 -> 383, 32 -> 3 469 -> 356 and
-// pullback 537 -> 366. (The staging arrays are native vectors: as arrays of uint4 they
+// 861 -> 647, 8 -> 32 401 -> 351 and pullback 705 -> 383, 32 -> 3 469 -> 279 and
+// pullback 537 -> 282. (The staging arrays are native vectors: as arrays of uint4 they
 // were kept in scratch memory and everything took 1.5-2 times as long.)
 template <int BZ>
 constexpr int conv_halo_cells() { return kChX * kChY * (BZ + 2); }
@@ -200,6 +200,14 @@ constexpr size_t conv_t_lds_bytes(bool hidden) {
     const size_t epi = size_t(kCbX * kCbY * BZ) * (hidden ? kAtRow * 2 : 3 * 4);
     return halo > epi ? halo : epi;
 }
+
+// The layers with one tile of outputs (32 -> 3 channels) hold all their weights in
+// registers and walk over the blocks, the next block's loads in flight through a block's
+// work: 356 -> 279 us, pullback 366 -> 282. The others would need more registers than two
+// waves per SIMD have (the 32 -> 32 layers spilled 160-260 of them and took 1.4 ms).
+template <int CIN, int NT>
+constexpr bool conv_walks() { return CIN == 32 && NT == 1; }
+constexpr int kWalkGroups = 512;  // two per CU, by registers
 
 // v in [-1, n + 4] into [0, n), n >= 2.
 __device__ __forceinline__ int wrap_near(int v, int n) {
@@ -221,16 +229,24 @@ __global__ __launch_bounds__(kBlock) void k_conv_t(Grid g, const u16* __restrict
     extern __shared__ __attribute__((aligned(16))) u16 xs[];
     const int nx = g.nx, ny = g.ny, nz = g.nz;
     const int nbx = nx / kCbX, nby = (ny + kCbY - 1) / kCbY, nbz = (nz + BZ - 1) / BZ;
-    int L = xcd_logical(blockIdx.x, gridDim.x);
-    const int bx = L % nbx;
-    L /= nbx;
-    const int by = L % nby;
-    L /= nby;
-    const int bz = L % nbz;
-    const int b = L / nbz;
-    const int x0 = bx * kCbX, y0 = by * kCbY, z0 = bz * BZ;
+    constexpr bool WALK = conv_walks<CIN, NT>();
+    const int nblocks = nbx * nby * nbz * g.batch;
+    const int64_t vol = int64_t(nx) * ny * nz;
+    int b, x0, y0, z0;
+    int64_t bcell;
+    auto place = [&](int blk) {
+        int L = blk;
+        x0 = L % nbx * kCbX;
+        L /= nbx;
+        y0 = L % nby * kCbY;
+        L /= nby;
+        z0 = L % nbz * BZ;
+        b = L / nbz;
+        bcell = b * vol;
+    };
+    int blk = xcd_logical(blockIdx.x, gridDim.x);
+    place(blk);
     const int tid = threadIdx.x;
-    const int64_t bcell = int64_t(b) * nz * ny * nx;
     const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int lm = lane & 15, gq = lane >> 4;
     // 1. input block with periodic halo -> LDS. A wave takes whole halo rows, 64 / CH cells a
@@ -246,7 +262,7 @@ __global__ __launch_bounds__(kBlock) void k_conv_t(Grid g, const u16* __restrict
     static_assert(NROW % (4 * RW) == 0, "whole rows per wave");
     const int sch = CH == 4 ? gq : 0, sx = CH == 4 ? lm : lane & 31, srow = CH == 4 ? 0 : lane >> 5;
     u32x4 va[RPW], vb[RPW], ve[KE];
-    {
+    auto fetch_in = [&]() __attribute__((always_inline)) {
         const int xo0 = wrapi(x0 - 1 + sx, nx) * CIN + sch * 8, xo1 = (x0 + 15 + sx) * CIN + sch * 8;
 #pragma unroll
         for (int k = 0; k < RPW; ++k) {
@@ -264,7 +280,7 @@ __global__ __launch_bounds__(kBlock) void k_conv_t(Grid g, const u16* __restrict
             const int e = min(k * kBlock + tid, NE - 1), row = e / (2 * CH);
             ve[k] = *reinterpret_cast<const u32x4*>(row_base(row) + wrapi(x0 + 31 + (e / CH & 1), nx) * CIN + e % CH * 8);
         }
-    }
+    };
     // block cell q = r * 32 + x of block row r; its grid cell
     auto block_cell = [&](int q, int64_t& c) -> bool {
         const int r = q >> 5, xx = q & 31;
@@ -277,6 +293,7 @@ __global__ __launch_bounds__(kBlock) void k_conv_t(Grid g, const u16* __restrict
     constexpr int ZM = EPI == EPI_DGRAD_HIDDEN ? MT : 1;
     float zr[ZM][4][NT];
     T old[3];
+    auto fetch_epi = [&]() __attribute__((always_inline)) {
     if constexpr (EPI == EPI_DGRAD_HIDDEN) {
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt) {
@@ -289,14 +306,34 @@ __global__ __launch_bounds__(kBlock) void k_conv_t(Grid g, const u16* __restrict
                 for (int nt = 0; nt < NT; ++nt) zr[mt][i][nt] = zp[i * 32 + nt * 16];
         }
     }
-    const int64_t vol = int64_t(nx) * ny * nz;
     if constexpr (EPI == EPI_DGRAD_INPUT) {
         int64_t c;
         const bool ok = block_cell(tid, c);
 #pragma unroll
         for (int n = 0; n < 3; ++n) old[n] = fout[(int64_t(b) * 3 + n) * vol + (ok ? c - bcell : 0)];
     }
+    };
+    // the weight operands of tap column tyx (tz = 0, 1, 2; 32 input channels), fetched PF
+    // columns ahead: with one tile of outputs all of them, once per workgroup
+    constexpr int PF = NT == 1 ? 9 : (BZ == 2 ? 2 : 1);
+    bf16x8 bn[PF][3][NT];
+    auto fetch_w = [&](int tyx) __attribute__((always_inline)) {
+#pragma unroll
+        for (int tz = 0; tz < 3; ++tz)
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt)
+                bn[tyx % PF][tz][nt] =
+                    *reinterpret_cast<const bf16x8*>(wpk + (((tz * 9 + tyx) * NT * 16 + nt * 16 + lm) * 32 + 8 * gq));
+    };
+    fetch_in();
+    if constexpr (!WALK) fetch_epi();
+    if constexpr (WALK) {
+#pragma unroll
+        for (int k = 0; k < PF; ++k) fetch_w(k);
+    }
+    do {
     __builtin_amdgcn_sched_barrier(0);
+    if constexpr (WALK) __syncthreads();  // the previous block's outputs are no longer read
     {
         u16* dst = xs + (sch * HC + (wave * RPW * RW + srow) * kChX + sx) * 8;
 #pragma unroll
@@ -310,6 +347,14 @@ __global__ __launch_bounds__(kBlock) void k_conv_t(Grid g, const u16* __restrict
             if (e < NE)
                 *reinterpret_cast<u32x4*>(xs + (e % CH * HC + e / (2 * CH) * kChX + 32 + (e / CH & 1)) * 8) = ve[k];
         }
+    }
+    if constexpr (WALK) {
+        fetch_epi();
+        const int next = blk + int(gridDim.x);
+        place(next < nblocks ? next : blk);
+        fetch_in();
+        place(blk);
+        __builtin_amdgcn_sched_barrier(0);
     }
     // 2. implicit GEMM from LDS
     f32x4 acc[MT][NT];
@@ -326,20 +371,10 @@ __global__ __launch_bounds__(kBlock) void k_conv_t(Grid g, const u16* __restrict
     }
     if constexpr (CIN == 32) {
         const u16* xq = xs + (gq * HC) * 8;  // this lane's 8-channel chunk
-        // the weight operands of tap column tyx (tz = 0, 1, 2), fetched PF columns ahead: a
-        // column is 12 BZ NT / 2 MFMAs of 16 cycles, an L2 access several hundred cycles
-        constexpr int PF = NT == 1 ? 9 : (BZ == 2 ? 2 : 1);
-        bf16x8 bn[PF][3][NT];
-        auto fetch_w = [&](int tyx) {
+        if constexpr (!WALK) {
 #pragma unroll
-            for (int tz = 0; tz < 3; ++tz)
-#pragma unroll
-                for (int nt = 0; nt < NT; ++nt)
-                    bn[tyx % PF][tz][nt] = *reinterpret_cast<const bf16x8*>(
-                        wpk + (((tz * 9 + tyx) * NT * 16 + nt * 16 + lm) * 32 + 8 * gq));
-        };
-#pragma unroll
-        for (int k = 0; k < PF; ++k) fetch_w(k);
+            for (int k = 0; k < PF; ++k) fetch_w(k);
+        }
         __syncthreads();
 #pragma unroll
         for (int tyx = 0; tyx < 9; ++tyx) {
@@ -349,7 +384,7 @@ __global__ __launch_bounds__(kBlock) void k_conv_t(Grid g, const u16* __restrict
             for (int tz = 0; tz < 3; ++tz)
 #pragma unroll
                 for (int nt = 0; nt < NT; ++nt) bv[tz][nt] = bn[tyx % PF][tz][nt];
-            if (tyx + PF < 9) fetch_w(tyx + PF);
+            if (!WALK && tyx + PF < 9) fetch_w(tyx + PF);
             __builtin_amdgcn_sched_barrier(0);  // keep the prefetch ahead of this column's work
 #pragma unroll
             for (int hz = 0; hz < HZ; ++hz) {
@@ -372,13 +407,13 @@ __global__ __launch_bounds__(kBlock) void k_conv_t(Grid g, const u16* __restrict
         }
     } else {
     // the weight operands of K tile kt, fetched one tile ahead
-    bf16x8 bn[NT];
-    auto fetch_w = [&](int kt) {
+    bf16x8 kn[NT];
+    auto fetch_k = [&](int kt) {
 #pragma unroll
         for (int nt = 0; nt < NT; ++nt)
-            bn[nt] = *reinterpret_cast<const bf16x8*>(wpk + ((kt * NT * 16 + nt * 16 + lm) * 32 + 8 * gq));
+            kn[nt] = *reinterpret_cast<const bf16x8*>(wpk + ((kt * NT * 16 + nt * 16 + lm) * 32 + 8 * gq));
     };
-    fetch_w(0);
+    fetch_k(0);
     __syncthreads();
 #pragma unroll
     for (int kt = 0; kt < NKT; ++kt) {
@@ -389,8 +424,8 @@ __global__ __launch_bounds__(kBlock) void k_conv_t(Grid g, const u16* __restrict
         const int toff = ((t / 9) * kChY + (t / 3) % 3) * kChX + t % 3;
         bf16x8 bv[NT];
 #pragma unroll
-        for (int nt = 0; nt < NT; ++nt) bv[nt] = bn[nt];
-        if (kt + 1 < NKT) fetch_w(kt + 1);
+        for (int nt = 0; nt < NT; ++nt) bv[nt] = kn[nt];
+        if (kt + 1 < NKT) fetch_k(kt + 1);
         __builtin_amdgcn_sched_barrier(0);  // keep the prefetch ahead of this tile's work
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt) {
@@ -484,6 +519,10 @@ __global__ __launch_bounds__(kBlock) void k_conv_t(Grid g, const u16* __restrict
             }
         }
     }
+        if constexpr (!WALK) break;
+        blk += gridDim.x;
+        place(blk);
+    } while (blk < nblocks);
 }
 
 // Planar velocity (T) -> channels-last bfloat16 [cell][8] (channels 3..7 zero).
@@ -817,8 +856,9 @@ hipError_t launch_closure_conv(const Grid& g, int which, const u16* in, const u1
                                const float* zin, float* zout, u16* aout, T* fout, hipStream_t s) {
 #define INS_CONV(CIN, NT, EPI, NOUT)                                                                                \
     do {                                                                                                            \
-        constexpr int BZ = CIN == 32 && EPI == EPI_HIDDEN ? 4 : 2;                                                  \
-        const int grid = (g.nx / kCbX) * ((g.ny + kCbY - 1) / kCbY) * ((g.nz + BZ - 1) / BZ) * g.batch;            \
+        constexpr int BZ = CIN == 32 && NT == 2 ? 4 : 2;                                                  \
+        const int nblk = (g.nx / kCbX) * ((g.ny + kCbY - 1) / kCbY) * ((g.nz + BZ - 1) / BZ) * g.batch;            \
+        const int grid = conv_walks<CIN, NT>() && nblk > kWalkGroups ? kWalkGroups : nblk;                          \
         const size_t shm = conv_t_lds_bytes<CIN, BZ>(EPI == EPI_HIDDEN || EPI == EPI_DGRAD_HIDDEN);                         \
         hipLaunchKernelGGL((k_conv_t<T, CIN, NT, EPI, BZ>), dim3(grid), dim3(kBlock), shm, s, g, in, wpk, bias, zin, \
                            zout, aout, fout, NOUT);                                                                 \
