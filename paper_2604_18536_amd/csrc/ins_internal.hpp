@@ -280,7 +280,7 @@ template <typename T>
 hipError_t launch_wall_grad_vjp(const Grid& g, const T* gbar, double* pbar, hipStream_t s);
 template <typename T>
 hipError_t launch_wall_stage(const Grid& g, const T* w, const double* p, bool proj, const T* u0, T* y, bool yinit,
-                             double cy, T* wout, double cw, hipStream_t s);
+                             double cy, T* wout, double cw, hipStream_t s, const T* wprev = nullptr, double ry = 0.0, double rw = 0.0);
 template <typename T>
 hipError_t launch_wall_stage_vjp(const Grid& g, const T* w, const double* p, bool proj_u, const T* ybar, const T* un,
                                  const double* q, bool has_w, double cb, double cw, T* u0bar, int mode, T* ubar_out,

@@ -870,7 +870,7 @@ bool eddy_stage(ins_ctx c, const T* w, const double* p, bool proj, const T* u0, 
 template <typename T>
 // ymode: 0 reads the accumulator y, 1 starts it at u0, 2 forms it as
 // u0 + (wprev - u0)/3 + 2 (w - u0)/3 from the unprojected stage inputs (RK4's
-// third stage, periodic 3D only; wprev may be wout's buffer).
+// third stage, uniform periodic and channel 3D only; wprev may be wout's buffer).
 void stage(ins_ctx c, const T* w, const double* p, bool proj, const T* u0, T* y, int ymode, double cy, T* wout,
            double cw, const char* label = nullptr, const T* wprev = nullptr) {
     const bool yinit = ymode == 1;
@@ -879,8 +879,15 @@ void stage(ins_ctx c, const T* w, const double* p, bool proj, const T* u0, T* y,
                              : !proj ? (y ? "stage_first" : "stage_first_rec")
                                      : (y ? (wout ? (ymode == 2 ? "stage_yw" : "stage") : "stage_last") : "stage_rec");
     if (ymode == 2) {
-        if (c->f32all() || c->gen || c->walls || c->g.dim != 3 || !proj || !y || !wout || !wprev)
-            raise(INS_ERR_UNSUPPORTED, "accumulator from the stage inputs: periodic 3D projected stages only");
+        if (c->f32all() || c->gen || c->g.dim != 3 || !proj || !y || !wout || !wprev)
+            raise(INS_ERR_UNSUPPORTED, "accumulator from the stage inputs: 3D projected stages only");
+        if (c->walls) {
+            c->launch(name, [&] {
+                return ins::launch_wall_stage<T>(c->g, w, p, true, u0, y, false, cy, wout, cw, c->stream, wprev, 1.0 / 3.0,
+                                                 2.0 / 3.0);
+            });
+            return;
+        }
         if (eddy_stage<T>(c, w, p, true, u0, y, false, cy, wout, cw, wprev)) return;
         const T* mc = closure_at_stage<T>(c, w, p);
         c->launch(name, [&] {
@@ -1065,12 +1072,12 @@ void step_rk4(ins_ctx c, const T* u0, T* u1, double dt, const Stages<T>* keep = 
     double* P2 = keep ? keep->p[0] : p;
     double* P3 = keep ? keep->p[1] : p;
     double* P4 = keep ? keep->p[2] : p;
-    // On the periodic 3D grid the first two stages store only W2 = u0 + dt/2 F1
+    // On 3D grids (periodic, channel) the first two stages store only W2 = u0 + dt/2 F1
     // and W3 = u0 + dt/2 F2: the third forms the accumulator
     // u0 + dt/6 F1 + dt/3 F2 = u0 + (W2 - u0)/3 + 2 (W3 - u0)/3 from W2 (read
     // pointwise before W4 overwrites it) and the u0 and W3 it reads anyway
     // (72 bytes per cell less traffic per step in float64).
-    const bool yw = !c->f32all() && !c->gen && !c->walls && c->g.dim == 3;
+    const bool yw = !c->f32all() && !c->gen && c->g.dim == 3;
     stage<T>(c, u0, nullptr, false, u0, yw ? nullptr : y, 1, dt / 6.0, W2, dt / 2.0);
     poisson(c, W2, nullptr, P2);
     stage<T>(c, W2, P2, true, u0, yw ? nullptr : y, 0, dt / 3.0, W3, dt / 2.0);

@@ -347,11 +347,18 @@ struct WallLds {
 // 2.54 ms). The float32 instance is no longer held to 64 registers (8 waves
 // per SIMD): with its loads in flight it spilled 80-96 bytes there and ran
 // at the old speed; uncapped it takes 84-88 registers (5 waves).
-template <typename T, bool PROJ, int TX, int TY, int PT>
+//
+// YW: the accumulator is y = u0 + ry (wprev - u0) + rw (w - u0), as in k_stage_zm: RK4's
+// first two stages then neither store nor read y (72 bytes per cell in float64;
+// 512 x 256 x 256: first stage 540 -> 408 us, second 927 -> 612, third 927 -> 957, a
+// step 6.21 -> 5.83 ms, float32 5.00 -> 4.64). wprev may be the buffer wout writes (each
+// cell's wprev is read one plane before that cell's output is written); w at the own
+// cell is read as a third stream.
+template <typename T, bool PROJ, int TX, int TY, int PT, bool YW = false>
 __global__ __launch_bounds__(TX * TY) void k_wall_stage_zm(Grid g, const T* __restrict__ w,
                                                              const double* __restrict__ p, const T* __restrict__ u0,
-                                                             T* __restrict__ y, int yinit, T cy, T* __restrict__ wout,
-                                                             T cw, int zc) {
+                                                             T* __restrict__ y, int yinit, T cy, T* wout, T cw, int zc,
+                                                             const T* wprev, T ry, T rw) {
     constexpr int NT = TX * TY, HX = TX + 2, HP = HX * (TY + 2);
     constexpr int NS = (HP + NT - 1) / NT;
     __shared__ T ring[4][3][HP];
@@ -443,14 +450,16 @@ __global__ __launch_bounds__(TX * TY) void k_wall_stage_zm(Grid g, const T* __re
     };
     // pointwise streams of the plane computed next: issued after the current
     // plane's stores, used at the next plane's stores
-    T pbase[3] = {T(0), T(0), T(0)}, pyv[3] = {T(0), T(0), T(0)};
+    T pbase[3] = {T(0), T(0), T(0)}, pyv[3] = {T(0), T(0), T(0)}, pwc[3] = {T(0), T(0), T(0)};
+    const T* ysrc = YW ? wprev : y;
     auto fetch_point = [&](int z) {
         const int c0 = z * plane + cxy;
 #pragma unroll
         for (int a = 0; a < 3; ++a) {
             const int64_t kk = boff + int64_t(a) * nc + c0;
             if constexpr (LB) pbase[a] = __builtin_nontemporal_load(u0 + kk);
-            if constexpr (LY) pyv[a] = __builtin_nontemporal_load(y + kk);
+            if constexpr (LY) pyv[a] = __builtin_nontemporal_load(ysrc + kk);
+            if constexpr (YW) pwc[a] = w[kk];
         }
     };
 
@@ -477,7 +486,7 @@ __global__ __launch_bounds__(TX * TY) void k_wall_stage_zm(Grid g, const T* __re
                 const int64_t kk = boff + int64_t(a) * nc + c0;
                 const bool zero = a == 1 && wallrow;
                 const T base = LB ? pbase[a] : T(0);
-                const T yv = LY ? pyv[a] : base;
+                const T yv = YW ? base + ry * (pyv[a] - base) + rw * (pwc[a] - base) : (LY ? pyv[a] : base);
                 if (y) __builtin_nontemporal_store(zero ? T(0) : yv + cy * F[a], y + kk);
                 if (wout) __builtin_nontemporal_store(zero ? T(0) : base + cw * F[a], wout + kk);
             }
@@ -1403,32 +1412,32 @@ static void wall_stage_dim(const Grid& g, const T* w, const double* p, bool proj
 
 template <typename T>
 hipError_t launch_wall_stage(const Grid& g, const T* w, const double* p, bool proj, const T* u0, T* y, bool yinit,
-                             double cy, T* wout, double cw, hipStream_t s) {
+                             double cy, T* wout, double cw, hipStream_t s, const T* wprev, double ry, double rw) {
     if (g.dim == 3) {
         constexpr int TX = 64, TY = 8;
         const int yi = yinit ? 1 : 0;
         // pointwise streams: u0 when it seeds the stage register or the
         // accumulator, y when the accumulator is read
         const int pt = ((wout || yinit) ? 1 : 0) | ((y && !yinit) ? 2 : 0);
-#define INS_WSZM(PR, PTI)                                                                                            \
+#define INS_WSZM(PR, PTI, YWI)                                                                                       \
     do {                                                                                                             \
-        constexpr auto kern = &k_wall_stage_zm<T, PR, TX, TY, PTI>;                                                  \
+        constexpr auto kern = &k_wall_stage_zm<T, PR, TX, TY, PTI, YWI>;                                             \
         /* float32: at most 32 planes (512 x 256 x 256: stage 550 -> 505 us against 64) */                           \
         const int zc = zm_chunk(g, TX, TY, resident_groups<kern, TX * TY>(), sizeof(T) == 8 ? 64 : 32);              \
         const int nblk = ((g.nx + TX - 1) / TX) * ((g.ny + TY - 1) / TY) * ((g.nz + zc - 1) / zc) * g.batch;         \
-        hipLaunchKernelGGL((k_wall_stage_zm<T, PR, TX, TY, PTI>), dim3(nblk), dim3(TX * TY), 0, s, g, w, p, u0, y,   \
-                           yi, T(cy), wout, T(cw), zc);                                                              \
+        hipLaunchKernelGGL((k_wall_stage_zm<T, PR, TX, TY, PTI, YWI>), dim3(nblk), dim3(TX * TY), 0, s, g, w, p, u0, \
+                           y, yi, T(cy), wout, T(cw), zc, wprev, T(ry), T(rw));                                      \
     } while (0)
-        if (proj && pt == 3)
-            INS_WSZM(true, 3);
-        else if (proj && pt == 2)
-            INS_WSZM(true, 2);
-        else if (proj)
-            INS_WSZM(true, 1);
+        if (wprev)
+            INS_WSZM(true, 3, true);
         else if (pt == 3)
-            INS_WSZM(false, 3);
+            return hipErrorInvalidValue;  // no schedule reads both u0 and y otherwise
+        else if (proj && pt == 2)
+            INS_WSZM(true, 2, false);
+        else if (proj)
+            INS_WSZM(true, 1, false);
         else
-            INS_WSZM(false, 1);
+            INS_WSZM(false, 1, false);
 #undef INS_WSZM
     } else
         wall_stage_dim<T, 2>(g, w, p, proj, u0, y, yinit ? 1 : 0, T(cy), wout, T(cw), s);
@@ -1555,7 +1564,7 @@ hipError_t launch_cg_weighted_center(const Grid& g, double* t, double* msum, dou
     template hipError_t launch_wall_div_vjp<T>(const Grid&, const double*, T*, hipStream_t);                         \
     template hipError_t launch_wall_grad_vjp<T>(const Grid&, const T*, double*, hipStream_t);                        \
     template hipError_t launch_wall_stage<T>(const Grid&, const T*, const double*, bool, const T*, T*, bool, double, \
-                                             T*, double, hipStream_t);                                               \
+                                             T*, double, hipStream_t, const T*, double, double);                     \
     template hipError_t launch_wall_stage_vjp<T>(const Grid&, const T*, const double*, bool, const T*, const T*,     \
                                                  const double*, bool, double, double, T*, int, T*, hipStream_t);     \
     template hipError_t launch_cg_div<T>(const Grid&, const T*, const double*, double*, double*, int, hipStream_t);
