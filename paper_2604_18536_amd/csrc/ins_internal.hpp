@@ -248,7 +248,7 @@ hipError_t launch_fill_zero_f(float* p, size_t n, hipStream_t s);
 // Learned closure (bfloat16 MFMA convolutions). Activations are channels-last
 // bfloat16 stored as 16-bit words.
 template <typename T>
-hipError_t launch_closure_pack_input(const Grid& g, const T* u, unsigned short* x0, hipStream_t s);
+hipError_t launch_closure_pack_input(const Grid& g, const T* w, const double* p, unsigned short* x0, hipStream_t s);
 hipError_t launch_closure_pack_weights(const float* w, int cin, int cout, int cinp, int ntf, unsigned short* wf,
                                        int coutp, int ntd, unsigned short* wd, hipStream_t s);
 // which: 0, 1 hidden layers, 2 output layer; 10, 11 dgrad into hidden layers; 12 dgrad to the input.

@@ -771,11 +771,12 @@ void eddy_alloc(ins_ctx c) {
     closure_alloc_common(c);
 }
 
-// m = m_theta(u); leaves x0, z1, a1, z2, a2 for a following pullback. Without
+// m = m_theta(u), for the network u = (p ? u - G p : u); leaves x0, z1, a1, z2, a2 for a
+// following pullback. Without
 // need_m the learned closure's output layer and the eddy term itself are left out: the
 // pullbacks read a2 or nu_t and the cotangent, not m.
 template <typename T>
-void closure_forward(ins_ctx c, const T* u, T* m, bool keep_z = true, bool need_m = true) {
+void closure_forward(ins_ctx c, const T* u, T* m, bool keep_z = true, bool need_m = true, const double* p = nullptr) {
     const ins::Grid& g = c->g;
     if (c->clos_kind == 2) {
         c->eddy_u = u;
@@ -793,7 +794,7 @@ void closure_forward(ins_ctx c, const T* u, T* m, bool keep_z = true, bool need_
     // the float32 pre-activations are kept only when a pullback will need them
     float* z1 = keep_z ? c->z1 : nullptr;
     float* z2 = keep_z ? c->z2 : nullptr;
-    c->launch("cnn_pack_input", [&] { return ins::launch_closure_pack_input<T>(g, u, c->x0, c->stream); });
+    c->launch("cnn_pack_input", [&] { return ins::launch_closure_pack_input<T>(g, u, p, c->x0, c->stream); });
     c->launch("cnn_conv1", [&] {
         return ins::launch_closure_conv<T>(g, 0, c->x0, c->wf[0], c->theta + kB1, nullptr, z1, c->a1, nullptr, c->stream);
     });
@@ -819,7 +820,7 @@ void closure_backward(ins_ctx c, const T* mbar, T* ubar) {
         });
         return;
     }
-    c->launch("cnn_pack_cotangent", [&] { return ins::launch_closure_pack_input<T>(g, mbar, c->gm, c->stream); });
+    c->launch("cnn_pack_cotangent", [&] { return ins::launch_closure_pack_input<T>(g, mbar, nullptr, c->gm, c->stream); });
     c->launch("cnn_dgrad3", [&] {
         return ins::launch_closure_conv<T>(g, 10, c->gm, c->wd[2], nullptr, c->z2, nullptr, c->gz2, nullptr, c->stream);
     });
@@ -844,13 +845,17 @@ void closure_backward(ins_ctx c, const T* mbar, T* ubar) {
 template <typename T>
 const T* closure_at_stage(ins_ctx c, const T* w, const double* p, bool keep_z = false, bool need_m = true) {
     if (!c->clos_on) return nullptr;
+    T* m = static_cast<T*>(c->mclos);
+    if (c->clos_kind == 1) {  // the network's input is packed from w and p
+        closure_forward<T>(c, w, m, keep_z, need_m, p);
+        return m;
+    }
     const T* u = w;
     if (p) {
         T* ui = static_cast<T*>(c->ui);
         apply_projection<T>(c, w, p, ui);
         u = ui;
     }
-    T* m = static_cast<T*>(c->mclos);
     closure_forward<T>(c, u, m, keep_z, need_m);
     return m;
 }

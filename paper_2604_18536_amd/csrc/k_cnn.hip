@@ -25,6 +25,8 @@ namespace ins {
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef unsigned short u16;
 
 constexpr int kTaps = 27;
@@ -130,6 +132,11 @@ __device__ __forceinline__ void gelu_grad_n(const float (&z)[N], float (&d)[N]) 
 }
 
 __device__ __forceinline__ int wrapi(int v, int n) { return v < 0 ? v + n : (v >= n ? v - n : v); }
+// Output channel of column lm of tile nt: with two tiles (32 channels) a lane holds two
+// neighbouring channels, which it stores (and reads, z) as one value.
+template <int NT>
+__host__ __device__ __forceinline__ constexpr int out_chan(int nt, int lm) { return NT == 2 ? 2 * lm + nt : nt * 16 + lm; }
+
 // K tile kt, lane group gq: which tap and which first channel the lane's 8 operands hold.
 template <int CIN>
 __device__ __forceinline__ void ktile_tap(int kt, int gq, int& tap, int& c0) {
@@ -146,7 +153,8 @@ enum { EPI_HIDDEN = 0, EPI_OUT = 1, EPI_DGRAD_HIDDEN = 2, EPI_DGRAD_INPUT = 3 };
 
 // Implicit-GEMM 3x3x3 convolution over all cells of the batch.
 //   in   : [cells][CIN] bfloat16
-//   wpk  : [NKT][NT*16][32] bfloat16 packed weights (zero where k or n is padding)
+//   wpk  : [NKT][NT*16][32] bfloat16 packed weights (zero where k or n is padding; column
+//          nt * 16 + lm holds output channel out_chan(nt, lm))
 //   EPI_HIDDEN      : z = acc + bias -> zout [cells][32] fp32 (unless null), a = bf16(gelu(z)) -> aout [cells][32]
 //   EPI_OUT         : m[b][n][cell] = acc + bias (n < nout), field type T (planar velocity layout)
 //   EPI_DGRAD_HIDDEN: zbar = acc * gelu'(zin[cell][n]) -> aout [cells][32] bf16
@@ -181,9 +189,9 @@ __device__ __forceinline__ int conv_row(int wave, int mt) { return (mt >> 1) * k
 // loads of the input block are in flight together (before: one round trip of 4 per
 // thread after the other), as are the z or cotangent values the epilogue reads (before:
 // round trips through LDS or one at a time after the products); the 3-channel outputs
-// are written as whole rows. 32 -> 32 676 -> 579 (464 GFLOP: 0.8 PFLOP/s) and pullback
-// 861 -> 647, 8 -> 32 401 -> 351 and pullback 705 -> 383, 32 -> 3 469 -> 279 and
-// pullback 537 -> 282. (The staging arrays are native vectors: as arrays of uint4 they
+// are written as whole rows. 32 -> 32 676 -> 575 (464 GFLOP: 0.8 PFLOP/s) and pullback
+// 861 -> 650, 8 -> 32 401 -> 341 and pullback 705 -> 385, 32 -> 3 469 -> 279 and
+// pullback 537 -> 280. (The staging arrays are native vectors: as arrays of uint4 they
 // were kept in scratch memory and everything took 1.5-2 times as long.)
 template <int BZ>
 constexpr int conv_halo_cells() { return kChX * kChY * (BZ + 2); }
@@ -299,11 +307,13 @@ __global__ __launch_bounds__(kBlock) void k_conv_t(Grid g, const u16* __restrict
         for (int mt = 0; mt < MT; ++mt) {
             const int r = conv_row(wave, mt);
             const int yy = min(y0 + r % kCbY, ny - 1), zz = min(z0 + r / kCbY, nz - 1);
-            const float* zp = zin + (bcell + (int64_t(zz) * ny + yy) * nx + x0 + (mt & 1) * 16 + 4 * gq) * 32 + lm;
+            const float* zp = zin + (bcell + (int64_t(zz) * ny + yy) * nx + x0 + (mt & 1) * 16 + 4 * gq) * 32 + 2 * lm;
 #pragma unroll
-            for (int i = 0; i < 4; ++i)
-#pragma unroll
-                for (int nt = 0; nt < NT; ++nt) zr[mt][i][nt] = zp[i * 32 + nt * 16];
+            for (int i = 0; i < 4; ++i) {
+                const f32x2 z2 = *reinterpret_cast<const f32x2*>(zp + i * 32);
+                zr[mt][i][0] = z2[0];
+                zr[mt][i][NT - 1] = z2[1];
+            }
         }
     }
     if constexpr (EPI == EPI_DGRAD_INPUT) {
@@ -447,12 +457,13 @@ __global__ __launch_bounds__(kBlock) void k_conv_t(Grid g, const u16* __restrict
     constexpr int NCELL = kCbX * kCbY * BZ;
     __syncthreads();  // every wave is done reading the input block
     if constexpr (EPI == EPI_HIDDEN || EPI == EPI_DGRAD_HIDDEN) {
-        // z (if kept) from the registers, 64-byte runs; the bfloat16 output through LDS
+        // z (if kept) from the registers, a cell's 128 bytes at once; the bfloat16 output
+        // through LDS
         u16* at = xs;
         float bv[NT];
         if constexpr (EPI == EPI_HIDDEN)
 #pragma unroll
-            for (int nt = 0; nt < NT; ++nt) bv[nt] = bias[nt * 16 + lm];
+            for (int nt = 0; nt < NT; ++nt) bv[nt] = bias[out_chan<NT>(nt, lm)];
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt) {
             const int qb = conv_row(wave, mt) * 32 + (mt & 1) * 16 + 4 * gq;  // four cells of a row
@@ -468,23 +479,20 @@ __global__ __launch_bounds__(kBlock) void k_conv_t(Grid g, const u16* __restrict
                 }
             if constexpr (EPI == EPI_HIDDEN) {
                 if (zout && ok) {
-                    float* zp = zout + c * 32 + lm;
+                    float* zp = zout + c * 32 + 2 * lm;
 #pragma unroll
-                    for (int i = 0; i < 4; ++i)
-#pragma unroll
-                        for (int nt = 0; nt < NT; ++nt) zp[i * 32 + nt * 16] = z[i * NT + nt];
+                    for (int i = 0; i < 4; ++i) *reinterpret_cast<f32x2*>(zp + i * 32) = f32x2{z[i * NT], z[i * NT + 1]};
                 }
                 gelu_n(z, o);
             } else {
                 gelu_grad_n(z, o);
             }
 #pragma unroll
-            for (int i = 0; i < 4; ++i)
-#pragma unroll
-                for (int nt = 0; nt < NT; ++nt) {
-                    const float v = EPI == EPI_HIDDEN ? o[i * NT + nt] : acc[mt][nt][i] * o[i * NT + nt];
-                    at[(qb + i) * kAtRow + nt * 16 + lm] = bf16_bits(v);
-                }
+            for (int i = 0; i < 4; ++i) {
+                f32x2 v = {o[i * NT], o[i * NT + 1]};
+                if constexpr (EPI == EPI_DGRAD_HIDDEN) v = f32x2{acc[mt][0][i] * v[0], acc[mt][1][i] * v[1]};
+                *reinterpret_cast<bf16x2*>(at + (qb + i) * kAtRow + 2 * lm) = __builtin_convertvector(v, bf16x2);
+            }
         }
         __syncthreads();
 #pragma unroll
@@ -525,16 +533,33 @@ __global__ __launch_bounds__(kBlock) void k_conv_t(Grid g, const u16* __restrict
     } while (blk < nblocks);
 }
 
-// Planar velocity (T) -> channels-last bfloat16 [cell][8] (channels 3..7 zero).
-template <typename T>
-__global__ __launch_bounds__(kBlock) void k_pack_input(int64_t ncells, int64_t vol, const T* __restrict__ u,
+// Planar velocity u = w - G p (PROJ: float64 projection rounded to T; else w) ->
+// channels-last bfloat16 [cell][8] (channels 3..7 zero). Bound by its bytes: 300 MB at
+// 4 x 128^3 float32; projecting in a launch of its own wrote u and read it again (97 us
+// for the two, 54 us here).
+template <typename T, bool PROJ>
+__global__ __launch_bounds__(kBlock) void k_pack_input(Grid g, const T* __restrict__ w, const double* __restrict__ p,
                                                          u16* __restrict__ x0) {
     const int64_t c = int64_t(blockIdx.x) * kBlock + threadIdx.x;
-    if (c >= ncells) return;
-    const int64_t b = c / vol, r = c - b * vol;
+    const int64_t vol = g.ncell;
+    if (c >= vol * g.batch) return;
+    const int64_t b = c / vol;
+    const int r = int(c - b * vol);
+    T u[3];
+#pragma unroll
+    for (int a = 0; a < 3; ++a) u[a] = w[(b * 3 + a) * vol + r];
+    if constexpr (PROJ) {
+        const int row = r / g.nx, x = r - row * g.nx, z = row / g.ny, y = row - z * g.ny;
+        const double* pb = p + b * vol;
+        const double pc = pb[r];
+        const double dp[3] = {pb[x + 1 == g.nx ? r + 1 - g.nx : r + 1] - pc, pb[y + 1 == g.ny ? r + g.nx - g.nx * g.ny : r + g.nx] - pc,
+                              pb[z + 1 == g.nz ? row % g.ny * g.nx + x : r + g.nx * g.ny] - pc};
+#pragma unroll
+        for (int a = 0; a < 3; ++a) u[a] = T(double(u[a]) - dp[a] * g.ih[a]);
+    }
     u16 v[8] = {0, 0, 0, 0, 0, 0, 0, 0};
 #pragma unroll
-    for (int a = 0; a < 3; ++a) v[a] = bf16_bits(float(u[(b * 3 + a) * vol + r]));
+    for (int a = 0; a < 3; ++a) v[a] = bf16_bits(float(u[a]));
     uint4 out;
     out.x = v[0] | (unsigned(v[1]) << 16);
     out.y = v[2] | (unsigned(v[3]) << 16);
@@ -544,7 +569,7 @@ __global__ __launch_bounds__(kBlock) void k_pack_input(int64_t ncells, int64_t v
 }
 
 // FP32 parameters -> packed bfloat16 forward and dgrad weights.
-// Forward layer (cin, cout): wf[kt][n][32], K tile kt covering (tap, channel) as in ktile_tap<CINP>.
+// Forward layer (cin, cout): wf[kt][column][32] (out_chan gives the column's n), K tile kt covering (tap, channel) as in ktile_tap<CINP>.
 // Dgrad of the layer: a convolution from cout channels to cin channels with
 // W'[n = i][k = (t', o)] = W[o][i][26 - t'].
 __global__ void k_pack_weights(const float* __restrict__ w, int cin, int cout, int cinp, int ntf, u16* __restrict__ wf,
@@ -555,7 +580,8 @@ __global__ void k_pack_weights(const float* __restrict__ w, int cin, int cout, i
     const int totd = nktd * ntd * 16 * 32;
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i < totf) {
-        const int kk = i & 31, n = (i >> 5) % (ntf * 16), kt = i / (32 * ntf * 16);
+        const int kk = i & 31, col = (i >> 5) % (ntf * 16), kt = i / (32 * ntf * 16);
+        const int n = ntf == 2 ? out_chan<2>(col >> 4, col & 15) : col;
         const int gq = kk >> 3, j = kk & 7;
         int tap, c;
         if (cinp == 32) {
@@ -570,7 +596,8 @@ __global__ void k_pack_weights(const float* __restrict__ w, int cin, int cout, i
         wf[i] = bf16_bits(v);
     } else if (i < totf + totd) {
         const int e = i - totf;
-        const int kk = e & 31, n = (e >> 5) % (ntd * 16), kt = e / (32 * ntd * 16);
+        const int kk = e & 31, col = (e >> 5) % (ntd * 16), kt = e / (32 * ntd * 16);
+        const int n = ntd == 2 ? out_chan<2>(col >> 4, col & 15) : col;
         const int gq = kk >> 3, j = kk & 7;
         int tap, o;
         if (coutp == 32) {
@@ -835,9 +862,12 @@ __global__ __launch_bounds__(64 * kReduceRows) void k_wgrad_reduce(const float* 
 // Launchers
 // ----------------------------------------------------------------------------
 template <typename T>
-hipError_t launch_closure_pack_input(const Grid& g, const T* u, u16* x0, hipStream_t s) {
-    const int64_t vol = int64_t(g.nx) * g.ny * g.nz, n = vol * g.batch;
-    hipLaunchKernelGGL(k_pack_input<T>, dim3(int((n + kBlock - 1) / kBlock)), dim3(kBlock), 0, s, n, vol, u, x0);
+hipError_t launch_closure_pack_input(const Grid& g, const T* w, const double* p, u16* x0, hipStream_t s) {
+    const dim3 grid(int((g.ncell * g.batch + kBlock - 1) / kBlock));
+    if (p)
+        hipLaunchKernelGGL((k_pack_input<T, true>), grid, dim3(kBlock), 0, s, g, w, p, x0);
+    else
+        hipLaunchKernelGGL((k_pack_input<T, false>), grid, dim3(kBlock), 0, s, g, w, p, x0);
     return hipGetLastError();
 }
 
@@ -913,8 +943,8 @@ size_t closure_wgrad_partial_floats(int64_t ncells) {
     return size_t(wgrad_grid(ncells)) * (32 * kTaps * 32 + 32);
 }
 
-template hipError_t launch_closure_pack_input<double>(const Grid&, const double*, u16*, hipStream_t);
-template hipError_t launch_closure_pack_input<float>(const Grid&, const float*, u16*, hipStream_t);
+template hipError_t launch_closure_pack_input<double>(const Grid&, const double*, const double*, u16*, hipStream_t);
+template hipError_t launch_closure_pack_input<float>(const Grid&, const float*, const double*, u16*, hipStream_t);
 template hipError_t launch_closure_conv<double>(const Grid&, int, const u16*, const u16*, const float*, const float*,
                                                 float*, u16*, double*, hipStream_t);
 template hipError_t launch_closure_conv<float>(const Grid&, int, const u16*, const u16*, const float*, const float*,
