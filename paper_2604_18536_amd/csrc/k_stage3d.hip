@@ -1,7 +1,7 @@
 // Fused RK4 stage for 3D grids as a 2.5D z-march (the forward counterpart of
 // k_stage in k_stencil.hip; same arithmetic, different data movement).
 //
-// A workgroup owns a 64 x 8 tile of an x-y plane (the reverse stage: 32 x 8)
+// A workgroup owns a 64 x 8 tile of an x-y plane (the reverse stage: 32 x 8 or 64 x 8)
 // and a chunk of consecutive z planes. For every plane it forms the stage
 // velocity u = w - G p (float64 projection, Sec. 2.6.2) on the tile plus a
 // one-cell halo exactly once and
@@ -15,10 +15,7 @@
 
 namespace ins {
 
-constexpr int kZmTX = 32, kZmTY = 8;  // reverse-stage tile
-constexpr int kZmHX = kZmTX + 2, kZmHY = kZmTY + 2, kZmHP = kZmHX * kZmHY;  // 340 halo-plane cells
-
-template <typename T, int HX = kZmHX, int HP = kZmHP>
+template <typename T, int HX, int HP>
 struct LdsSrc {
     const T* zm;  // ring slot of plane z-1
     const T* z0;  // plane z
@@ -373,16 +370,18 @@ namespace ins {
 // velocity u_i = w - G p and the right-hand-side cotangent
 // Fbar_i = cb ybar + cw (un - G q) on the tile plus halo; four slots each and
 // the same load/compute pipeline as k_stage_zm.
-template <typename T, bool PROJ_U, bool HAS_W>
-__global__ __launch_bounds__(kBlock) void k_stage_vjp_zm(Grid g, const T* __restrict__ w, const double* __restrict__ p,
+template <typename T, bool PROJ_U, bool HAS_W, int TX, int TY>
+__global__ __launch_bounds__(TX * TY) void k_stage_vjp_zm(Grid g, const T* __restrict__ w, const double* __restrict__ p,
                                                            const T* __restrict__ ybar, const T* __restrict__ un,
                                                            const double* __restrict__ q, T cb, T cw,
                                                            T* __restrict__ u0bar, int mode, T* __restrict__ ubar_out,
                                                            int zc, T* __restrict__ fbar_out) {
-    __shared__ T ru[3][3][kZmHP];
-    __shared__ T rf[3][3][kZmHP];
+    constexpr int NT = TX * TY, HX = TX + 2, HP = HX * (TY + 2);
+    extern __shared__ __align__(16) unsigned char vjp_smem[];
+    auto* ru = reinterpret_cast<T(*)[3][HP]>(vjp_smem);
+    auto* rf = ru + 3;
     const int nx = g.nx, ny = g.ny, nz = g.nz;
-    const int ntx = (nx + kZmTX - 1) / kZmTX, nty = (ny + kZmTY - 1) / kZmTY, nzc = (nz + zc - 1) / zc;
+    const int ntx = (nx + TX - 1) / TX, nty = (ny + TY - 1) / TY, nzc = (nz + zc - 1) / zc;
     int L = xcd_logical(blockIdx.x, gridDim.x);
     const int tx = L % ntx;
     L /= ntx;
@@ -390,7 +389,7 @@ __global__ __launch_bounds__(kBlock) void k_stage_vjp_zm(Grid g, const T* __rest
     L /= nty;
     const int zci = L % nzc;
     const int b = L / nzc;
-    const int x0 = tx * kZmTX, y0 = ty * kZmTY, z0 = zci * zc;
+    const int x0 = tx * TX, y0 = ty * TY, z0 = zci * zc;
     const int z1 = min(z0 + zc, nz);
     const int64_t boff = int64_t(b) * 3 * g.ncell;
     const int64_t soff = int64_t(b) * g.ncell;
@@ -405,19 +404,19 @@ __global__ __launch_bounds__(kBlock) void k_stage_vjp_zm(Grid g, const T* __rest
     int hq[2], hxy[2], hxp[2], hyp[2];
 #pragma unroll
     for (int s = 0; s < 2; ++s) {
-        const int qi = threadIdx.x + s * kBlock;
+        const int qi = threadIdx.x + s * NT;
         hq[s] = qi;
-        const int qq = qi < kZmHP ? qi : 0;
-        const int gx = pmod(x0 - 1 + qq % kZmHX, nx);
-        const int gy = pmod(y0 - 1 + qq / kZmHX, ny);
+        const int qq = qi < HP ? qi : 0;
+        const int gx = pmod(x0 - 1 + qq % HX, nx);
+        const int gy = pmod(y0 - 1 + qq / HX, ny);
         hxy[s] = gy * nx + gx;
         hxp[s] = gy * nx + (gx + 1 == nx ? 0 : gx + 1);
         hyp[s] = (gy + 1 == ny ? 0 : gy + 1) * nx + gx;
     }
-    const int lx = threadIdx.x % kZmTX, ly = threadIdx.x / kZmTX;
+    const int lx = threadIdx.x % TX, ly = threadIdx.x / TX;
     const int cxg = x0 + lx, cyg = y0 + ly;
     const bool valid = cxg < nx && cyg < ny;
-    const int centre = (ly + 1) * kZmHX + (lx + 1);
+    const int centre = (ly + 1) * HX + (lx + 1);
 
     if constexpr (!(PROJ_U && HAS_W && sizeof(T) == 8)) {
         // Raw halo loads (w, ybar and, with PROJ_U / HAS_W, p and un, q at the
@@ -463,15 +462,15 @@ __global__ __launch_bounds__(kBlock) void k_stage_vjp_zm(Grid g, const T* __rest
             T* sf = &rf[k % 3][0][0];
 #pragma unroll
             for (int s = 0; s < 2; ++s) {
-                if (hq[s] < kZmHP) {
+                if (hq[s] < HP) {
 #pragma unroll
                     for (int c = 0; c < 3; ++c) {
                         T uv = hw[s][c];
                         if constexpr (PROJ_U) uv = T(double(hw[s][c]) - (hp[s][c + 1] - hp[s][0]) * g.ih[c]);
                         T fv = cb * hy[s][c];
                         if constexpr (HAS_W) fv += cw * T(double(hu[s][c]) - (hqv[s][c + 1] - hqv[s][0]) * g.ih[c]);
-                        su[c * kZmHP + hq[s]] = uv;
-                        sf[c * kZmHP + hq[s]] = fv;
+                        su[c * HP + hq[s]] = uv;
+                        sf[c * HP + hq[s]] = fv;
                     }
                 }
             }
@@ -501,8 +500,8 @@ __global__ __launch_bounds__(kBlock) void k_stage_vjp_zm(Grid g, const T* __rest
         for (int k = 2; k < nk; ++k) {
             const int z = z0 + k - 2;
             fetch_raw(pmod(z0 - 1 + min(k + 1, nk - 1), nz));
-            LdsSrc<T> U{&ru[(k - 2) % 3][0][0], &ru[(k - 1) % 3][0][0], &ru[k % 3][0][0], centre};
-            LdsSrc<T> F{&rf[(k - 2) % 3][0][0], &rf[(k - 1) % 3][0][0], &rf[k % 3][0][0], centre};
+            LdsSrc<T, HX, HP> U{&ru[(k - 2) % 3][0][0], &ru[(k - 1) % 3][0][0], &ru[k % 3][0][0], centre};
+            LdsSrc<T, HX, HP> F{&rf[(k - 2) % 3][0][0], &rf[(k - 1) % 3][0][0], &rf[k % 3][0][0], centre};
             T out[3];
             rhs_vjp_cell<T, 3>(g, U, F, Nb{}, out);
             if (valid) {
@@ -532,7 +531,7 @@ __global__ __launch_bounds__(kBlock) void k_stage_vjp_zm(Grid g, const T* __rest
         const int zpo = (zz + 1 == nz ? 0 : zz + 1) * plane;
 #pragma unroll
         for (int s = 0; s < 2; ++s) {
-            if (hq[s] < kZmHP) {
+            if (hq[s] < HP) {
                 const int j = zoff + hxy[s];
                 const int jp[3] = {zoff + hxp[s], zoff + hyp[s], zpo + hxy[s]};
                 double pc = 0.0, qc = 0.0;
@@ -556,11 +555,11 @@ __global__ __launch_bounds__(kBlock) void k_stage_vjp_zm(Grid g, const T* __rest
         T* sf = &rf[k % 3][0][0];
 #pragma unroll
         for (int s = 0; s < 2; ++s) {
-            if (hq[s] < kZmHP) {
+            if (hq[s] < HP) {
 #pragma unroll
                 for (int c = 0; c < 3; ++c) {
-                    su[c * kZmHP + hq[s]] = pu[s][c];
-                    sf[c * kZmHP + hq[s]] = pf[s][c];
+                    su[c * HP + hq[s]] = pu[s][c];
+                    sf[c * HP + hq[s]] = pf[s][c];
                 }
             }
         }
@@ -613,8 +612,8 @@ __global__ __launch_bounds__(kBlock) void k_stage_vjp_zm(Grid g, const T* __rest
         if (more) fetch_point(z + 1);
         if (valid) {
             const int c0 = z * plane + cyg * nx + cxg;
-            LdsSrc<T> U{&ru[(k - 2) % 3][0][0], &ru[(k - 1) % 3][0][0], &ru[k % 3][0][0], centre};
-            LdsSrc<T> F{&rf[(k - 2) % 3][0][0], &rf[(k - 1) % 3][0][0], &rf[k % 3][0][0], centre};
+            LdsSrc<T, HX, HP> U{&ru[(k - 2) % 3][0][0], &ru[(k - 1) % 3][0][0], &ru[k % 3][0][0], centre};
+            LdsSrc<T, HX, HP> F{&rf[(k - 2) % 3][0][0], &rf[(k - 1) % 3][0][0], &rf[k % 3][0][0], centre};
             T out[3];
             rhs_vjp_cell<T, 3>(g, U, F, Nb{}, out);
 #pragma unroll
@@ -632,20 +631,19 @@ __global__ __launch_bounds__(kBlock) void k_stage_vjp_zm(Grid g, const T* __rest
     }
 }
 
-template <typename T>
-hipError_t launch_stage_vjp_zm(const Grid& g, const T* w, const double* p, bool proj_u, const T* ybar, const T* un,
-                               const double* q, bool has_w, double cb, double cw, T* u0bar, int mode, T* ubar_out,
-                               hipStream_t s, T* fbar_out) {
-    if (has_w && cw == 0.0) return hipErrorInvalidValue;  // un - G q is recovered through 1 / cw
+template <typename T, int TX, int TY>
+void launch_stage_vjp_zm_tile(const Grid& g, const T* w, const double* p, bool proj_u, const T* ybar, const T* un,
+                              const double* q, bool has_w, double cb, double cw, T* u0bar, int mode, T* ubar_out,
+                              hipStream_t s, T* fbar_out) {
     const T tb = T(cb), tw = T(cw);
 #define INS_VJP_ZM(PU, HW)                                                                                            \
     do {                                                                                                              \
-        constexpr auto kern = &k_stage_vjp_zm<T, PU, HW>;                                                             \
-        const int zc = zm_chunk(g, kZmTX, kZmTY, resident_groups<kern, kBlock>(), 32);                            \
-        const int nblk =                                                                                              \
-            ((g.nx + kZmTX - 1) / kZmTX) * ((g.ny + kZmTY - 1) / kZmTY) * ((g.nz + zc - 1) / zc) * g.batch;           \
-        hipLaunchKernelGGL((k_stage_vjp_zm<T, PU, HW>), dim3(nblk), dim3(kBlock), 0, s, g, w, p, ybar, un, q, tb, tw, \
-                           u0bar, mode, ubar_out, zc, fbar_out);                                                      \
+        constexpr auto kern = &k_stage_vjp_zm<T, PU, HW, TX, TY>;                                                     \
+        constexpr int lds = 18 * (TX + 2) * (TY + 2) * int(sizeof(T));                                                \
+        const int zc = zm_chunk(g, TX, TY, resident_groups<kern, TX * TY, lds>(), 32);                                \
+        const int nblk = ((g.nx + TX - 1) / TX) * ((g.ny + TY - 1) / TY) * ((g.nz + zc - 1) / zc) * g.batch;          \
+        hipLaunchKernelGGL((k_stage_vjp_zm<T, PU, HW, TX, TY>), dim3(nblk), dim3(TX * TY), lds, s, g, w, p, ybar, un, \
+                           q, tb, tw, u0bar, mode, ubar_out, zc, fbar_out);                                           \
     } while (0)
     if (proj_u && has_w)
         INS_VJP_ZM(true, true);
@@ -656,6 +654,24 @@ hipError_t launch_stage_vjp_zm(const Grid& g, const T* w, const double* p, bool 
     else
         INS_VJP_ZM(false, false);
 #undef INS_VJP_ZM
+}
+
+// Tiles of 32 x 8. float32 takes 64 x 8 where that pads x no more: fewer halo lines per
+// row (a kept-stages pullback 256^3 3.22 -> 3.05 ms, 4 x 128^3 1.75 -> 1.68; 32^3, half
+// padding, 131 -> 141 us); in float64 its two rings would leave one workgroup per CU
+// (256^3 4.25 -> 4.29 ms).
+template <typename T>
+hipError_t launch_stage_vjp_zm(const Grid& g, const T* w, const double* p, bool proj_u, const T* ybar, const T* un,
+                               const double* q, bool has_w, double cb, double cw, T* u0bar, int mode, T* ubar_out,
+                               hipStream_t s, T* fbar_out) {
+    if (has_w && cw == 0.0) return hipErrorInvalidValue;  // un - G q is recovered through 1 / cw
+    if constexpr (sizeof(T) == 4)
+        if ((g.nx + 31) / 32 % 2 == 0) {
+            launch_stage_vjp_zm_tile<T, 64, 8>(g, w, p, proj_u, ybar, un, q, has_w, cb, cw, u0bar, mode, ubar_out, s,
+                                               fbar_out);
+            return hipGetLastError();
+        }
+    launch_stage_vjp_zm_tile<T, 32, 8>(g, w, p, proj_u, ybar, un, q, has_w, cb, cw, u0bar, mode, ubar_out, s, fbar_out);
     return hipGetLastError();
 }
 

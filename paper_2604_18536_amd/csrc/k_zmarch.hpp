@@ -5,15 +5,15 @@
 
 namespace ins {
 
-// Workgroups of NT threads of kernel K that the device holds at once (a constant
+// Workgroups of NT threads and LDS dynamic bytes of kernel K that the device holds at once (a constant
 // of the kernel and the device; asked once).
-template <auto K, int NT>
+template <auto K, int NT, int LDS = 0>
 int resident_groups() {
     static const int n = [] {
         int dev = 0, cus = 0, per = 0;
         if (hipGetDevice(&dev) != hipSuccess ||
             hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-            hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, reinterpret_cast<const void*>(K), NT, 0) != hipSuccess) {
+            hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, reinterpret_cast<const void*>(K), NT, LDS) != hipSuccess) {
             (void)hipGetLastError();
             return 512;
         }
