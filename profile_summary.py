@@ -51,8 +51,8 @@ VARIANT_ORDERS = {
     },
     # channel, direct pressure solve (FFTs along x and z, tridiagonal solves along y)
     "channel": {
-        "void ins::k_wall_stage_zm<double, true,": (["channel:stage", "channel:stage", "channel:stage_last"], _WALL),
-        "void ins::k_wall_stage_zm<double, false,": (["channel:stage_first"], _WALL),
+        "void ins::k_wall_stage_zm<double, true,": (["channel:stage_rec", "channel:stage_yw", "channel:stage_last"], _WALL),
+        "void ins::k_wall_stage_zm<double, false,": (["channel:stage_first_rec"], _WALL),
         "void ins::k_fft_x_fwd<double, 3, 3,": (["channel:fft_x_fwd_div"], ["k_fft.hip", "k_common.hpp"]),
         "void ins::k_fft_strided<0,": (["channel:fft_z_fwd"], ["k_fft.hip", "k_common.hpp"]),
         "void ins::k_channel_ysolve<": (["channel:channel_ysolve"], ["k_chsolve.hip", "k_common.hpp"]),
