@@ -302,26 +302,26 @@ __global__ __launch_bounds__(kBlock) void k_conv_t(Grid g, const u16* __restrict
     float zr[ZM][4][NT];
     T old[3];
     auto fetch_epi = [&]() __attribute__((always_inline)) {
-    if constexpr (EPI == EPI_DGRAD_HIDDEN) {
+        if constexpr (EPI == EPI_DGRAD_HIDDEN) {
 #pragma unroll
-        for (int mt = 0; mt < MT; ++mt) {
-            const int r = conv_row(wave, mt);
-            const int yy = min(y0 + r % kCbY, ny - 1), zz = min(z0 + r / kCbY, nz - 1);
-            const float* zp = zin + (bcell + (int64_t(zz) * ny + yy) * nx + x0 + (mt & 1) * 16 + 4 * gq) * 32 + 2 * lm;
+            for (int mt = 0; mt < MT; ++mt) {
+                const int r = conv_row(wave, mt);
+                const int yy = min(y0 + r % kCbY, ny - 1), zz = min(z0 + r / kCbY, nz - 1);
+                const float* zp = zin + (bcell + (int64_t(zz) * ny + yy) * nx + x0 + (mt & 1) * 16 + 4 * gq) * 32 + 2 * lm;
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const f32x2 z2 = *reinterpret_cast<const f32x2*>(zp + i * 32);
-                zr[mt][i][0] = z2[0];
-                zr[mt][i][NT - 1] = z2[1];
+                for (int i = 0; i < 4; ++i) {
+                    const f32x2 z2 = *reinterpret_cast<const f32x2*>(zp + i * 32);
+                    zr[mt][i][0] = z2[0];
+                    zr[mt][i][NT - 1] = z2[1];
+                }
             }
         }
-    }
-    if constexpr (EPI == EPI_DGRAD_INPUT) {
-        int64_t c;
-        const bool ok = block_cell(tid, c);
+        if constexpr (EPI == EPI_DGRAD_INPUT) {
+            int64_t c;
+            const bool ok = block_cell(tid, c);
 #pragma unroll
-        for (int n = 0; n < 3; ++n) old[n] = fout[(int64_t(b) * 3 + n) * vol + (ok ? c - bcell : 0)];
-    }
+            for (int n = 0; n < 3; ++n) old[n] = fout[(int64_t(b) * 3 + n) * vol + (ok ? c - bcell : 0)];
+        }
     };
     // the weight operands of tap column tyx (tz = 0, 1, 2; 32 input channels), fetched PF
     // columns ahead: with one tile of outputs all of them, once per workgroup
@@ -342,191 +342,191 @@ __global__ __launch_bounds__(kBlock) void k_conv_t(Grid g, const u16* __restrict
         for (int k = 0; k < PF; ++k) fetch_w(k);
     }
     do {
-    __builtin_amdgcn_sched_barrier(0);
-    if constexpr (WALK) __syncthreads();  // the previous block's outputs are no longer read
-    {
-        u16* dst = xs + (sch * HC + (wave * RPW * RW + srow) * kChX + sx) * 8;
-#pragma unroll
-        for (int k = 0; k < RPW; ++k) {
-            *reinterpret_cast<u32x4*>(dst + k * RW * kChX * 8) = va[k];
-            if constexpr (CH == 4) *reinterpret_cast<u32x4*>(dst + (k * RW * kChX + 16) * 8) = vb[k];
-        }
-#pragma unroll
-        for (int k = 0; k < KE; ++k) {
-            const int e = k * kBlock + tid;
-            if (e < NE)
-                *reinterpret_cast<u32x4*>(xs + (e % CH * HC + e / (2 * CH) * kChX + 32 + (e / CH & 1)) * 8) = ve[k];
-        }
-    }
-    if constexpr (WALK) {
-        fetch_epi();
-        const int next = blk + int(gridDim.x);
-        place(next < nblocks ? next : blk);
-        fetch_in();
-        place(blk);
         __builtin_amdgcn_sched_barrier(0);
-    }
-    // 2. implicit GEMM from LDS
-    f32x4 acc[MT][NT];
+        if constexpr (WALK) __syncthreads();  // the previous block's outputs are no longer read
+        {
+            u16* dst = xs + (sch * HC + (wave * RPW * RW + srow) * kChX + sx) * 8;
 #pragma unroll
-    for (int mt = 0; mt < MT; ++mt)
+            for (int k = 0; k < RPW; ++k) {
+                *reinterpret_cast<u32x4*>(dst + k * RW * kChX * 8) = va[k];
+                if constexpr (CH == 4) *reinterpret_cast<u32x4*>(dst + (k * RW * kChX + 16) * 8) = vb[k];
+            }
 #pragma unroll
-        for (int nt = 0; nt < NT; ++nt) acc[mt][nt] = f32x4{0.f, 0.f, 0.f, 0.f};
-    int hbase[MT];  // halo cell of (tap offset 0, 0, 0) for this lane's row of each M tile
-#pragma unroll
-    for (int mt = 0; mt < MT; ++mt) {
-        const int r = conv_row(wave, mt);
-        const int yy = r % kCbY, zz = r / kCbY;
-        hbase[mt] = (zz * kChY + yy) * kChX + (mt & 1) * 16 + lm;
-    }
-    if constexpr (CIN == 32) {
-        const u16* xq = xs + (gq * HC) * 8;  // this lane's 8-channel chunk
-        if constexpr (!WALK) {
-#pragma unroll
-            for (int k = 0; k < PF; ++k) fetch_w(k);
+            for (int k = 0; k < KE; ++k) {
+                const int e = k * kBlock + tid;
+                if (e < NE)
+                    *reinterpret_cast<u32x4*>(xs + (e % CH * HC + e / (2 * CH) * kChX + 32 + (e / CH & 1)) * 8) = ve[k];
+            }
         }
-        __syncthreads();
+        if constexpr (WALK) {
+            fetch_epi();
+            const int next = blk + int(gridDim.x);
+            place(next < nblocks ? next : blk);
+            fetch_in();
+            place(blk);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        // 2. implicit GEMM from LDS
+        f32x4 acc[MT][NT];
 #pragma unroll
-        for (int tyx = 0; tyx < 9; ++tyx) {
-            const int ty = tyx / 3, tx = tyx % 3;
-            bf16x8 bv[3][NT];
+        for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
-            for (int tz = 0; tz < 3; ++tz)
+            for (int nt = 0; nt < NT; ++nt) acc[mt][nt] = f32x4{0.f, 0.f, 0.f, 0.f};
+        int hbase[MT];  // halo cell of (tap offset 0, 0, 0) for this lane's row of each M tile
 #pragma unroll
-                for (int nt = 0; nt < NT; ++nt) bv[tz][nt] = bn[tyx % PF][tz][nt];
-            if (!WALK && tyx + PF < 9) fetch_w(tyx + PF);
-            __builtin_amdgcn_sched_barrier(0);  // keep the prefetch ahead of this column's work
+        for (int mt = 0; mt < MT; ++mt) {
+            const int r = conv_row(wave, mt);
+            const int yy = r % kCbY, zz = r / kCbY;
+            hbase[mt] = (zz * kChY + yy) * kChX + (mt & 1) * 16 + lm;
+        }
+        if constexpr (CIN == 32) {
+            const u16* xq = xs + (gq * HC) * 8;  // this lane's 8-channel chunk
+            if constexpr (!WALK) {
 #pragma unroll
-            for (int hz = 0; hz < HZ; ++hz) {
+                for (int k = 0; k < PF; ++k) fetch_w(k);
+            }
+            __syncthreads();
 #pragma unroll
-                for (int xh = 0; xh < 2; ++xh) {
-                    // halo cell of source plane hz for output row (y = wave) and x half xh
-                    const int cell = (hz * kChY + wave + ty) * kChX + xh * 16 + lm + tx;
-                    const bf16x8 av = *reinterpret_cast<const bf16x8*>(xq + cell * 8);
+            for (int tyx = 0; tyx < 9; ++tyx) {
+                const int ty = tyx / 3, tx = tyx % 3;
+                bf16x8 bv[3][NT];
 #pragma unroll
-                    for (int zz = 0; zz < BZ; ++zz) {
-                        const int tz = hz - zz;
-                        if (tz < 0 || tz > 2) continue;
+                for (int tz = 0; tz < 3; ++tz)
 #pragma unroll
-                        for (int nt = 0; nt < NT; ++nt)
-                            acc[zz * 2 + xh][nt] =
-                                __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, bv[tz][nt], acc[zz * 2 + xh][nt], 0, 0, 0);
+                    for (int nt = 0; nt < NT; ++nt) bv[tz][nt] = bn[tyx % PF][tz][nt];
+                if (!WALK && tyx + PF < 9) fetch_w(tyx + PF);
+                __builtin_amdgcn_sched_barrier(0);  // keep the prefetch ahead of this column's work
+#pragma unroll
+                for (int hz = 0; hz < HZ; ++hz) {
+#pragma unroll
+                    for (int xh = 0; xh < 2; ++xh) {
+                        // halo cell of source plane hz for output row (y = wave) and x half xh
+                        const int cell = (hz * kChY + wave + ty) * kChX + xh * 16 + lm + tx;
+                        const bf16x8 av = *reinterpret_cast<const bf16x8*>(xq + cell * 8);
+#pragma unroll
+                        for (int zz = 0; zz < BZ; ++zz) {
+                            const int tz = hz - zz;
+                            if (tz < 0 || tz > 2) continue;
+#pragma unroll
+                            for (int nt = 0; nt < NT; ++nt)
+                                acc[zz * 2 + xh][nt] =
+                                    __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, bv[tz][nt], acc[zz * 2 + xh][nt], 0, 0, 0);
+                        }
                     }
                 }
             }
-        }
-    } else {
-    // the weight operands of K tile kt, fetched one tile ahead
-    bf16x8 kn[NT];
-    auto fetch_k = [&](int kt) {
+        } else {
+            // the weight operands of K tile kt, fetched one tile ahead
+            bf16x8 kn[NT];
+            auto fetch_k = [&](int kt) {
 #pragma unroll
-        for (int nt = 0; nt < NT; ++nt)
-            kn[nt] = *reinterpret_cast<const bf16x8*>(wpk + ((kt * NT * 16 + nt * 16 + lm) * 32 + 8 * gq));
-    };
-    fetch_k(0);
-    __syncthreads();
+                for (int nt = 0; nt < NT; ++nt)
+                    kn[nt] = *reinterpret_cast<const bf16x8*>(wpk + ((kt * NT * 16 + nt * 16 + lm) * 32 + 8 * gq));
+            };
+            fetch_k(0);
+            __syncthreads();
 #pragma unroll
-    for (int kt = 0; kt < NKT; ++kt) {
-        int tap, c0;
-        ktile_tap<CIN>(kt, gq, tap, c0);
-        const bool tap_ok = tap < kTaps;
-        const int t = tap_ok ? tap : 0;
-        const int toff = ((t / 9) * kChY + (t / 3) % 3) * kChX + t % 3;
-        bf16x8 bv[NT];
+            for (int kt = 0; kt < NKT; ++kt) {
+                int tap, c0;
+                ktile_tap<CIN>(kt, gq, tap, c0);
+                const bool tap_ok = tap < kTaps;
+                const int t = tap_ok ? tap : 0;
+                const int toff = ((t / 9) * kChY + (t / 3) % 3) * kChX + t % 3;
+                bf16x8 bv[NT];
 #pragma unroll
-        for (int nt = 0; nt < NT; ++nt) bv[nt] = kn[nt];
-        if (kt + 1 < NKT) fetch_k(kt + 1);
-        __builtin_amdgcn_sched_barrier(0);  // keep the prefetch ahead of this tile's work
+                for (int nt = 0; nt < NT; ++nt) bv[nt] = kn[nt];
+                if (kt + 1 < NKT) fetch_k(kt + 1);
+                __builtin_amdgcn_sched_barrier(0);  // keep the prefetch ahead of this tile's work
 #pragma unroll
-        for (int mt = 0; mt < MT; ++mt) {
-            bf16x8 av;
-            if (tap_ok) {
-                av = *reinterpret_cast<const bf16x8*>(xs + (hbase[mt] + toff) * 8);
-            } else {
+                for (int mt = 0; mt < MT; ++mt) {
+                    bf16x8 av;
+                    if (tap_ok) {
+                        av = *reinterpret_cast<const bf16x8*>(xs + (hbase[mt] + toff) * 8);
+                    } else {
 #pragma unroll
-                for (int j = 0; j < 8; ++j) av[j] = __bf16(0.0f);
-            }
+                        for (int j = 0; j < 8; ++j) av[j] = __bf16(0.0f);
+                    }
 #pragma unroll
-            for (int nt = 0; nt < NT; ++nt)
-                acc[mt][nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, bv[nt], acc[mt][nt], 0, 0, 0);
-        }
-    }
-    }
-    // 3. epilogue: lane holds D[m = 4 gq + i][n = nt*16 + lm] of M tile mt, i.e. block
-    // cell q = r * 32 + (mt & 1) * 16 + 4 gq + i with r = conv_row(wave, mt)
-    constexpr int NCELL = kCbX * kCbY * BZ;
-    __syncthreads();  // every wave is done reading the input block
-    if constexpr (EPI == EPI_HIDDEN || EPI == EPI_DGRAD_HIDDEN) {
-        // z (if kept) from the registers, a cell's 128 bytes at once; the bfloat16 output
-        // through LDS
-        u16* at = xs;
-        float bv[NT];
-        if constexpr (EPI == EPI_HIDDEN)
-#pragma unroll
-            for (int nt = 0; nt < NT; ++nt) bv[nt] = bias[out_chan<NT>(nt, lm)];
-#pragma unroll
-        for (int mt = 0; mt < MT; ++mt) {
-            const int qb = conv_row(wave, mt) * 32 + (mt & 1) * 16 + 4 * gq;  // four cells of a row
-            int64_t c;
-            const bool ok = block_cell(qb, c);
-            float z[4 * NT], o[4 * NT];
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-#pragma unroll
-                for (int nt = 0; nt < NT; ++nt) {
-                    if constexpr (EPI == EPI_HIDDEN) z[i * NT + nt] = acc[mt][nt][i] + bv[nt];
-                    else z[i * NT + nt] = zr[mt][i][nt];
+                    for (int nt = 0; nt < NT; ++nt)
+                        acc[mt][nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, bv[nt], acc[mt][nt], 0, 0, 0);
                 }
-            if constexpr (EPI == EPI_HIDDEN) {
-                if (zout && ok) {
-                    float* zp = zout + c * 32 + 2 * lm;
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) *reinterpret_cast<f32x2*>(zp + i * 32) = f32x2{z[i * NT], z[i * NT + 1]};
-                }
-                gelu_n(z, o);
-            } else {
-                gelu_grad_n(z, o);
-            }
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                f32x2 v = {o[i * NT], o[i * NT + 1]};
-                if constexpr (EPI == EPI_DGRAD_HIDDEN) v = f32x2{acc[mt][0][i] * v[0], acc[mt][1][i] * v[1]};
-                *reinterpret_cast<bf16x2*>(at + (qb + i) * kAtRow + 2 * lm) = __builtin_convertvector(v, bf16x2);
             }
         }
-        __syncthreads();
+        // 3. epilogue: lane holds D[m = 4 gq + i][n = nt*16 + lm] of M tile mt, i.e. block
+        // cell q = r * 32 + (mt & 1) * 16 + 4 gq + i with r = conv_row(wave, mt)
+        constexpr int NCELL = kCbX * kCbY * BZ;
+        __syncthreads();  // every wave is done reading the input block
+        if constexpr (EPI == EPI_HIDDEN || EPI == EPI_DGRAD_HIDDEN) {
+            // z (if kept) from the registers, a cell's 128 bytes at once; the bfloat16 output
+            // through LDS
+            u16* at = xs;
+            float bv[NT];
+            if constexpr (EPI == EPI_HIDDEN)
 #pragma unroll
-        for (int e = tid; e < NCELL * 4; e += kBlock) {  // 4 chunks per cell
-            const int q = e >> 2, ch = e & 3;
-            int64_t c;
-            if (block_cell(q, c))
-                *reinterpret_cast<uint4*>(aout + c * 32 + ch * 8) =
-                    *reinterpret_cast<const uint4*>(at + q * kAtRow + ch * 8);
-        }
-    } else {
-        static_assert(NCELL == kBlock, "one cell per thread");
-        float* ot = reinterpret_cast<float*>(xs);  // [3][cell]
-        if (lm < nout) {
+                for (int nt = 0; nt < NT; ++nt) bv[nt] = bias[out_chan<NT>(nt, lm)];
 #pragma unroll
             for (int mt = 0; mt < MT; ++mt) {
-                const int qb = conv_row(wave, mt) * 32 + (mt & 1) * 16 + 4 * gq;
-                *reinterpret_cast<f32x4*>(ot + lm * NCELL + qb) = acc[mt][0];
-            }
-        }
-        __syncthreads();
-        int64_t c;
-        if (block_cell(tid, c)) {
+                const int qb = conv_row(wave, mt) * 32 + (mt & 1) * 16 + 4 * gq;  // four cells of a row
+                int64_t c;
+                const bool ok = block_cell(qb, c);
+                float z[4 * NT], o[4 * NT];
 #pragma unroll
-            for (int n = 0; n < 3; ++n) {
-                T* dst = fout + (int64_t(b) * 3 + n) * vol + (c - bcell);
-                const float v = ot[n * NCELL + tid];
-                if constexpr (EPI == EPI_OUT)
-                    *dst = T(v + bias[n]);
-                else
-                    *dst = T(double(old[n]) + double(v));
+                for (int i = 0; i < 4; ++i)
+#pragma unroll
+                    for (int nt = 0; nt < NT; ++nt) {
+                        if constexpr (EPI == EPI_HIDDEN) z[i * NT + nt] = acc[mt][nt][i] + bv[nt];
+                        else z[i * NT + nt] = zr[mt][i][nt];
+                    }
+                if constexpr (EPI == EPI_HIDDEN) {
+                    if (zout && ok) {
+                        float* zp = zout + c * 32 + 2 * lm;
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) *reinterpret_cast<f32x2*>(zp + i * 32) = f32x2{z[i * NT], z[i * NT + 1]};
+                    }
+                    gelu_n(z, o);
+                } else {
+                    gelu_grad_n(z, o);
+                }
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    f32x2 v = {o[i * NT], o[i * NT + 1]};
+                    if constexpr (EPI == EPI_DGRAD_HIDDEN) v = f32x2{acc[mt][0][i] * v[0], acc[mt][1][i] * v[1]};
+                    *reinterpret_cast<bf16x2*>(at + (qb + i) * kAtRow + 2 * lm) = __builtin_convertvector(v, bf16x2);
+                }
+            }
+            __syncthreads();
+#pragma unroll
+            for (int e = tid; e < NCELL * 4; e += kBlock) {  // 4 chunks per cell
+                const int q = e >> 2, ch = e & 3;
+                int64_t c;
+                if (block_cell(q, c))
+                    *reinterpret_cast<uint4*>(aout + c * 32 + ch * 8) =
+                        *reinterpret_cast<const uint4*>(at + q * kAtRow + ch * 8);
+            }
+        } else {
+            static_assert(NCELL == kBlock, "one cell per thread");
+            float* ot = reinterpret_cast<float*>(xs);  // [3][cell]
+            if (lm < nout) {
+#pragma unroll
+                for (int mt = 0; mt < MT; ++mt) {
+                    const int qb = conv_row(wave, mt) * 32 + (mt & 1) * 16 + 4 * gq;
+                    *reinterpret_cast<f32x4*>(ot + lm * NCELL + qb) = acc[mt][0];
+                }
+            }
+            __syncthreads();
+            int64_t c;
+            if (block_cell(tid, c)) {
+#pragma unroll
+                for (int n = 0; n < 3; ++n) {
+                    T* dst = fout + (int64_t(b) * 3 + n) * vol + (c - bcell);
+                    const float v = ot[n * NCELL + tid];
+                    if constexpr (EPI == EPI_OUT)
+                        *dst = T(v + bias[n]);
+                    else
+                        *dst = T(double(old[n]) + double(v));
+                }
             }
         }
-    }
         if constexpr (!WALK) break;
         blk += gridDim.x;
         place(blk);
