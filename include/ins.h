@@ -249,7 +249,8 @@ ins_status ins_set_body_force(ins_ctx ctx, const double* force);
  * check_every < 0. */
 ins_status ins_cg_set(ins_ctx ctx, double rtol, int maxiter, int check_every);
 /* Iterations and final relative residual ||res|| / ||res_0|| of the last
- * CG solve (maxima over the batch; 0 and 0 before the first). Synchronises
+ * CG solve (maxima over the batch, NaN where a field's residual is not a
+ * number, e.g. where ||res_0||^2 overflows; 0 and 0 before the first). Synchronises
  * the context's stream. INS_ERR_UNSUPPORTED on a uniform periodic context. */
 ins_status ins_cg_info(ins_ctx ctx, int* iterations, double* relres);
 

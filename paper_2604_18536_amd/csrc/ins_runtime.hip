@@ -1890,7 +1890,8 @@ ins_status ins_cg_info(ins_ctx ctx, int* iterations, double* relres) {
         double rr = 0.0;
         for (int b = 0; b < ctx->g.batch; ++b) {
             it = std::max(it, ctx->cg_host[b].it);
-            rr = std::max(rr, ctx->cg_host[b].relres);
+            const double rel = ctx->cg_host[b].relres;
+            if (rel > rr || std::isnan(rel)) rr = rel;  // (a NaN stays: nothing compares greater)
         }
         *iterations = it;
         *relres = rr;
