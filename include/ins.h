@@ -248,6 +248,15 @@ ins_status ins_set_body_force(ins_ctx ctx, const double* force);
  * context (solved by FFT); INS_ERR_INVALID for rtol < 0, maxiter < 1 or
  * check_every < 0. */
 ins_status ins_cg_set(ins_ctx ctx, double rtol, int maxiter, int check_every);
+/* A field solved by one launch of several workgroups has them wait for each other, which
+ * needs all of them on the GPU at once. Where other work keeps some of them out for longer
+ * than `polls` polls (about a microsecond each; default 2^21), e.g. more such solves
+ * waiting for each other's workgroups than the GPU holds, from several processes or
+ * from graphs replayed on many streams, the field is solved again, from the same right-hand
+ * side, by one workgroup, which waits for nobody: the result is right to the same rtol, and
+ * takes up to some hundred times as long. 0: always so. Errors as ins_cg_set
+ * (INS_ERR_INVALID for polls < 0). */
+ins_status ins_cg_set_wait(ins_ctx ctx, int polls);
 /* Iterations and final relative residual ||res|| / ||res_0|| of the last
  * CG solve (maxima over the batch, NaN where a field's residual is not a
  * number, e.g. where ||res_0||^2 overflows; 0 and 0 before the first). Synchronises

@@ -288,10 +288,11 @@ hipError_t launch_wall_stage_vjp(const Grid& g, const T* w, const double* p, boo
 
 // Scalars of one field's conjugate-gradient solve that the host reads: rr_0,
 // the final rr and relres = sqrt(rr / rr_0), iterations done, stop flag (set
-// by each iteration's first kernel), mean of the right-hand side.
+// by each iteration's first kernel), mean of the right-hand side; failed: a workgroup of
+// the single-launch solve gave up waiting for the others.
 struct CgScal {
     double rr, rr0, relres, mean;
-    int it, done;
+    int it, done, failed;
 };
 // Work split of the CG kernels: workgroups per field (<= kCgMaxBlocks); every
 // partial-sum buffer holds cg_blocks(g) * batch doubles.
@@ -303,7 +304,7 @@ template <typename T>
 hipError_t launch_cg_div(const Grid& g, const T* vel, const double* rin, double* r, double* msum, int mode,
                          hipStream_t s);
 // r = w_j (mean_w - r) (modes 0-2; wsum = sum of w_j over a field) or mean - r
-// (mode 3); x = 0; partial sums of r.r into rb0; resets st.it / st.done.
+// (mode 3); x = 0; partial sums of r.r into rb0; resets st.it / st.done / st.failed.
 hipError_t launch_cg_init(const Grid& g, double* r, double* x, const double* msum, double* rb0, CgScal* st, int mode,
                           double wsum, hipStream_t s);
 // Iteration k: stop test from rr_k (partials rbk); x += alpha_{k-1} p_{k-1}
@@ -331,10 +332,13 @@ struct CgPlan {
     __host__ __device__ size_t words() const { return size_t(G) * (2 * dim * face * 2 + 8) * 2; }
 };
 CgPlan cg_plan(const Grid& g, int cus);
+// Polls (about 1 us each) before a workgroup's wait for the others gives up.
+constexpr unsigned kCgSpin = 1u << 21;
 // From r = b (x_0 = 0) and the partial sums rb0 of b.b: x and st of every field.
-// exch: P.words() * P.fields words (unused when P.G == 1).
-hipError_t launch_cg_solve(const Grid& g, const CgPlan& P, const double* r, double* x, const double* rb0, CgScal* st,
-                           void* exch, double rtol2, int maxiter, hipStream_t s);
+// exch: P.words() * P.fields words; p, q: scratch fields (all three unused when
+// P.G == 1). r is overwritten where a field is solved again alone.
+hipError_t launch_cg_solve(const Grid& g, const CgPlan& P, double* r, double* x, double* p, double* q, const double* rb0,
+                           CgScal* st, void* exch, double rtol2, int maxiter, unsigned spin, hipStream_t s);
 // t = w_j (t - mean_w(t)) in place (msum: partial-sum scratch).
 hipError_t launch_cg_weighted_center(const Grid& g, double* t, double* msum, double wsum, hipStream_t s);
 

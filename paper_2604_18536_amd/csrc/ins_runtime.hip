@@ -215,6 +215,7 @@ struct ins_ctx_s {
     ins::CgScal* cg_host = nullptr;  // pinned host copy of cg_st
     ins::CgPlan cg_pl{};             // single-launch solve (G = 0: the field does not fit)
     void* cg_exch = nullptr;         // words its workgroups exchange through
+    unsigned cg_spin = ins::kCgSpin;  // polls before one of them gives up waiting
     double* d_ym = nullptr;          // y metrics of the channel grid (Grid::ym)
     // stretched grid (a periodic direction, or the channel's x or z, given faces):
     // every operator from the per-direction metrics Grid::gm, pressure by CG
@@ -580,8 +581,8 @@ void cg_solve(ins_ctx c, const void* vel, const double* r, double* x, int mode) 
     const double rtol2 = c->cg_rtol * c->cg_rtol;
     if (c->cg_pl.G > 0) {
         c->launch("cg_solve", [&] {
-            return ins::launch_cg_solve(g, c->cg_pl, c->cg_r, x, rb[0], c->cg_st, c->cg_exch, rtol2, c->cg_maxiter,
-                                        c->stream);
+            return ins::launch_cg_solve(g, c->cg_pl, c->cg_r, x, c->cg_p[0], c->cg_p[1], rb[0], c->cg_st, c->cg_exch, rtol2,
+                                        c->cg_maxiter, c->cg_spin, c->stream);
         });
         return;
     }
@@ -1825,6 +1826,15 @@ ins_status ins_cg_set(ins_ctx ctx, double rtol, int maxiter, int check_every) {
         ctx->cg_rtol = rtol;
         ctx->cg_maxiter = maxiter;
         ctx->cg_check = check_every;
+    });
+}
+
+ins_status ins_cg_set_wait(ins_ctx ctx, int polls) {
+    return guarded([&] {
+        checked(ctx);
+        if (!ctx->walls && !ctx->gen) raise(INS_ERR_UNSUPPORTED, "the uniform periodic grid solves by FFT, not CG");
+        if (polls < 0) raise(INS_ERR_INVALID, "polls must be >= 0");
+        ctx->cg_spin = static_cast<unsigned>(polls);
     });
 }
 

@@ -32,8 +32,12 @@
 // All workgroups of a launch have to be resident together. The launch is
 // cooperative, and the plan uses at most a quarter of the workgroups the chip
 // holds, so that launches from the process's four hardware queues fit side by
-// side (a cooperative launch recorded into a graph replays as a plain one).
-// Every wait is bounded all the same: past the bound the field becomes NaN.
+// side (a cooperative launch recorded into a graph replays as a plain one). That
+// says nothing of other processes on the same GPU, so every wait is bounded: past
+// the bound a workgroup marks its field (CgScal::failed) and leaves, the others
+// follow, and k_cg_alone, launched behind every such solve, solves a marked field
+// again from r_0 with one workgroup, which waits for nobody. The caller gets a
+// solved field either way.
 #include <algorithm>
 
 #include "k_cg.hpp"
@@ -48,7 +52,6 @@ using u64 = unsigned long long;
 
 // Halo cells per thread of an instance.
 constexpr int cg_halo(int c) { return c > 12 ? 6 : 4; }
-constexpr unsigned kCgpSpin = 1u << 25;   // polls before a wait gives up (about half a minute)
 
 typedef unsigned int v4u __attribute__((ext_vector_type(4)));
 typedef __amdgpu_buffer_rsrc_t Rsrc;
@@ -70,10 +73,11 @@ __device__ __forceinline__ double value_of(v4u w) {
 }
 
 // Wait for this thread's N slots; all loads of a round go out together (no branch
-// between them). False: gave up.
+// between them). False: gave up after `spin` polls.
 template <int N>
-__device__ __forceinline__ bool collect(Rsrc base, const unsigned (&slot)[N], unsigned off, unsigned tag, double (&v)[N]) {
-    for (unsigned n = 0; n < kCgpSpin; ++n) {
+__device__ __forceinline__ bool collect(Rsrc base, const unsigned (&slot)[N], unsigned off, unsigned tag, double (&v)[N],
+                                        unsigned spin) {
+    for (unsigned n = 0; n < spin; ++n) {
         v4u w[N];
         asm volatile("" ::: "memory");
 #pragma unroll
@@ -91,11 +95,13 @@ __device__ __forceinline__ bool collect(Rsrc base, const unsigned (&slot)[N], un
 
 // Lane l of the first wave waits for sum l & 3 of the workgroups l >> 2,
 // (l >> 2) + 16, ... (four slots of two words per workgroup) and adds them.
-__device__ __forceinline__ bool collect_sum(Rsrc base, unsigned off, int groups, unsigned tag, double& sum) {
+__device__ __forceinline__ bool collect_sum(Rsrc base, unsigned off, int groups, unsigned tag, double& sum,
+                                            unsigned spin) {
     constexpr int NP = kCgMaxGroups / 16;
     const unsigned w0 = threadIdx.x >> 2;
     const unsigned slot0 = off + 8 * min(w0, unsigned(groups) - 1u) + 2 * (threadIdx.x & 3);
-    for (unsigned n = 0; n < kCgpSpin; ++n) {
+    sum = 0.0;
+    for (unsigned n = 0; n < spin; ++n) {
         v4u w[NP];
         asm volatile("" ::: "memory");
 #pragma unroll
@@ -147,6 +153,15 @@ __device__ __forceinline__ double met_id(const Grid& g, int a, int n, int i) {
     return a == 1 ? g.ym[(n + 2) + i + 1] : g.ih2[a];
 }
 
+// What a solve leaves for ins_cg_info.
+__device__ __forceinline__ void cg_report(CgScal& s, double rr, double rr0, int k) {
+    s.rr = rr;
+    s.rr0 = rr0;
+    s.relres = rr0 > 0.0 ? sqrt(rr / rr0) : 0.0;
+    s.it = k;
+    s.done = 1;
+}
+
 }  // namespace
 
 // NT threads, C consecutive cells each along the last direction (z; y in 2D):
@@ -157,7 +172,7 @@ template <int NT, int C, int DIM, bool MULTI>
 __global__ __launch_bounds__(NT, 2) void k_cg_solve(Grid g, CgPlan P, const double* __restrict__ r0,
                                                   double* __restrict__ x, const double* __restrict__ rb0,
                                                   CgScal* __restrict__ st, u64* __restrict__ ex, int field0,
-                                                  double rtol2, int maxiter) {
+                                                  double rtol2, int maxiter, unsigned spin) {
     // p on the block plus halo, the table of the last direction, (MULTI) q on the block
     extern __shared__ double pl[];
     __shared__ double sh[NT / 64][4], tot[4];
@@ -190,7 +205,8 @@ __global__ __launch_bounds__(NT, 2) void k_cg_solve(Grid g, CgPlan P, const doub
         const bool wall = M == 1 && wally && (o[M] + i == 0 || o[M] + i == n[M]);
         td[i] = wall ? 0.0 : met_id(g, M, n[M], o[M] + i - 1);
     }
-    if (tid == 0) lost = 0;
+    // (a workgroup that starts after another has given up need not wait its own bound out)
+    if (tid == 0) lost = MULTI && __hip_atomic_load(&st[f].failed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 
     // words of this field, for even and odd iterations: P.G * 2 * DIM outboxes of
     // P.face slots, then the four partial sums of each workgroup
@@ -319,8 +335,7 @@ __global__ __launch_bounds__(NT, 2) void k_cg_solve(Grid g, CgPlan P, const doub
     }
     double rr = rr0;
     int k = 0;
-    bool bad = false;
-    if (!cg_stopped(rr0, rr0, 0, rtol2, maxiter)) {
+    if (!lost && !cg_stopped(rr0, rr0, 0, rtol2, maxiter)) {
 #pragma unroll
         for (int j = 0; j < C; ++j)
             if (j < nc) pl[cell0 + j * sm] = p[j];
@@ -405,7 +420,7 @@ __global__ __launch_bounds__(NT, 2) void k_cg_solve(Grid g, CgPlan P, const doub
                     }
                     // lane l collects sum l & 3 of the workgroups l >> 2, (l >> 2) + 16, ...
                     double t;
-                    if (!collect_sum(fx, bx + red, P.G, tag, t)) lost = 1;
+                    if (!collect_sum(fx, bx + red, P.G, tag, t, spin)) lost = 1;
 #pragma unroll
                     for (int o = 4; o < 64; o <<= 1) t += __shfl_xor(t, o, 64);
                     if (tid < 4) tot[tid] = t;
@@ -416,10 +431,10 @@ __global__ __launch_bounds__(NT, 2) void k_cg_solve(Grid g, CgPlan P, const doub
                     hq[h] = 0.0;
                     if (hl[h] >= 0) post(fx, bx + ho[h], tag, ql[hb[h]]);
                 }
-                if (!collect<HALO>(fx, hs, bx, tag, hq)) lost = 1;
+                if (!collect<HALO>(fx, hs, bx, tag, hq, spin)) lost = 1;
                 __syncthreads();
-                if (lost) {
-                    bad = true;
+                if (lost) {  // x and st are then k_cg_alone's
+                    if (tid == 0) __hip_atomic_store(&st[f].failed, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                     break;
                 }
                 rr = tot[3];
@@ -455,18 +470,84 @@ __global__ __launch_bounds__(NT, 2) void k_cg_solve(Grid g, CgPlan P, const doub
             }
         }
     }
-    const double nan = __longlong_as_double(0x7ff8000000000000ll);
 #pragma unroll
     for (int j = 0; j < C; ++j)
-        if (j < nc) x[g0 + j * gm] = bad ? nan : xs[j];
-    if (wg == 0 && tid == 0) {
-        CgScal& s = st[f];
-        s.rr = bad ? nan : rr;
-        s.rr0 = rr0;
-        s.relres = rr0 > 0.0 ? sqrt(s.rr / rr0) : 0.0;
-        s.it = k;
-        s.done = 1;
+        if (j < nc) x[g0 + j * gm] = xs[j];
+    if (wg == 0 && tid == 0) cg_report(st[f], rr, rr0, k);
+}
+
+// The fields that k_cg_solve gave up, each by one workgroup through memory: r = r_0 and
+// the scratch fields p, q (r_0 is not needed afterwards); the same operator, recurrence
+// and stop test as a field of one workgroup. A field that was solved costs one read.
+constexpr int kCgAloneNT = 1024;
+template <int DIM>
+__global__ __launch_bounds__(kCgAloneNT) void k_cg_alone(Grid g, double* r, double* x, double* p, double* q,
+                                                         const double* __restrict__ rb0, CgScal* st, double rtol2,
+                                                         int maxiter) {
+    __shared__ double sh[kCgAloneNT / 64];
+    const int f = blockIdx.x;
+    if (!st[f].failed) return;
+    const int nx = g.nx, ny = g.ny, nz = DIM == 3 ? g.nz : 1, plane = nx * ny, n = int(g.ncell);
+    const bool wally = g.ywalls || !g.gm[0];
+    const int64_t foff = int64_t(f) * g.ncell;
+    r += foff;
+    x += foff;
+    p += foff;
+    q += foff;
+    // sum over the two neighbours of direction a of (p - p_neighbour) / d
+    auto pair = [&](int a, int len, int i, int stride, int c) {
+        const bool wall = a == 1 && wally;
+        const double pc = p[c];
+        double s = 0.0;
+        if (!(wall && i == 0)) s += (pc - p[i == 0 ? c + (len - 1) * stride : c - stride]) * met_id(g, a, len, i - 1);
+        if (!(wall && i == len - 1)) s += (pc - p[i == len - 1 ? c - (len - 1) * stride : c + stride]) * met_id(g, a, len, i);
+        return s;
+    };
+    auto apply = [&](int c) {
+        const int z = c / plane, y = c / nx - z * ny, cx = c % nx;
+        const double wx = met_w(g, 0, nx, cx), wy = met_w(g, 1, ny, y), wz = DIM == 3 ? met_w(g, 2, nz, z) : 1.0;
+        double v = wy * wz * pair(0, nx, cx, 1, c) + wx * wz * pair(1, ny, y, nx, c);
+        if constexpr (DIM == 3) v += wx * wy * pair(2, nz, z, plane, c);
+        return v;
+    };
+    double rr0 = 0.0;
+    const int np = cg_blocks_of(g);
+    for (int i = threadIdx.x; i < np; i += kCgAloneNT) rr0 += rb0[int64_t(f) * np + i];
+    rr0 = block_sum<kCgAloneNT>(rr0, sh);
+    for (int c = threadIdx.x; c < n; c += kCgAloneNT) {
+        x[c] = 0.0;
+        p[c] = r[c];
     }
+    double rr = rr0;
+    int k = 0;
+    while (!cg_stopped(rr, rr0, k, rtol2, maxiter)) {
+        __syncthreads();  // p is read at neighbouring cells
+        double s = 0.0;
+        for (int c = threadIdx.x; c < n; c += kCgAloneNT) {
+            const double v = apply(c);
+            q[c] = v;
+            s += p[c] * v;
+        }
+        const double pq = block_sum<kCgAloneNT>(s, sh);
+        if (!(pq > 0.0)) {
+            rr = 0.0;
+            break;
+        }
+        const double alpha = rr / pq;
+        s = 0.0;
+        for (int c = threadIdx.x; c < n; c += kCgAloneNT) {
+            x[c] += alpha * p[c];
+            const double v = r[c] - alpha * q[c];
+            r[c] = v;
+            s += v * v;
+        }
+        const double rrm = rr;
+        rr = block_sum<kCgAloneNT>(s, sh);
+        ++k;
+        const double beta = rr / rrm;
+        for (int c = threadIdx.x; c < n; c += kCgAloneNT) p[c] = r[c] + beta * p[c];
+    }
+    if (threadIdx.x == 0) cg_report(st[f], rr, rr0, k);
 }
 
 __global__ __launch_bounds__(kBlock) void k_cg_clear(u64* p, int64_t n) {
@@ -575,8 +656,8 @@ CgPlan cg_plan(const Grid& g, int cus) {
     return CgPlan{};
 }
 
-hipError_t launch_cg_solve(const Grid& g, const CgPlan& P, const double* r, double* x, const double* rb0, CgScal* st,
-                           void* exch, double rtol2, int maxiter, hipStream_t s) {
+hipError_t launch_cg_solve(const Grid& g, const CgPlan& P, double* r, double* x, double* p, double* q, const double* rb0,
+                           CgScal* st, void* exch, double rtol2, int maxiter, unsigned spin, hipStream_t s) {
     Grid ga = g;
     CgPlan pa = P;
     u64* ex = static_cast<u64*>(exch);
@@ -585,7 +666,7 @@ hipError_t launch_cg_solve(const Grid& g, const CgPlan& P, const double* r, doub
     const int step = P.G == 1 ? g.batch : P.fields;
     for (int f0 = 0; f0 < g.batch; f0 += step) {
         const int nf = std::min(step, g.batch - f0);
-        void* args[] = {&ga, &pa, &r, &x, &rb0, &st, &ex, &f0, &rtol2, &maxiter};
+        void* args[] = {&ga, &pa, &r, &x, &rb0, &st, &ex, &f0, &rtol2, &maxiter, &spin};
         hipError_t e;
         if (P.G == 1) {
             e = hipLaunchKernel(kern, dim3(nf), dim3(P.nt), args, lds, s);
@@ -598,7 +679,12 @@ hipError_t launch_cg_solve(const Grid& g, const CgPlan& P, const double* r, doub
         }
         if (e != hipSuccess) return e;
     }
-    return hipSuccess;
+    if (P.G == 1) return hipSuccess;
+    if (g.dim == 3)
+        hipLaunchKernelGGL((k_cg_alone<3>), dim3(g.batch), dim3(kCgAloneNT), 0, s, g, r, x, p, q, rb0, st, rtol2, maxiter);
+    else
+        hipLaunchKernelGGL((k_cg_alone<2>), dim3(g.batch), dim3(kCgAloneNT), 0, s, g, r, x, p, q, rb0, st, rtol2, maxiter);
+    return hipGetLastError();
 }
 
 }  // namespace ins

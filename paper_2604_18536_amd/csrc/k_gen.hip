@@ -635,6 +635,7 @@ __global__ __launch_bounds__(kBlock) void k_gen_cg_init(Grid g, double* __restri
             st[c.b].mean = mean;
             st[c.b].it = 0;
             st[c.b].done = 0;
+            st[c.b].failed = 0;
         }
     }
 }

@@ -944,6 +944,7 @@ __global__ __launch_bounds__(kBlock) void k_cg_init(Grid g, double* __restrict__
             st[c.b].mean = mean;
             st[c.b].it = 0;
             st[c.b].done = 0;
+            st[c.b].failed = 0;
         }
     }
 }

@@ -35,3 +35,64 @@ def test_a_residual_that_is_not_a_number_is_reported(n):
     s.poisson_solve(dev(np.stack([S.random_scalar(n, 8 + b) for b in range(3)])))
     assert 0.0 < s.cg_info()[1] <= 1e-10
     s.close()
+
+
+# sizes of 2, 4, 8, 10 and 20 cells per thread (a 2D channel, 3D channels)
+WAIT_SIZES = [(96, 77), (24, 20, 12), (50, 49, 47), (66, 61, 50), (66, 81, 48), (79, 77, 80)]
+
+
+@pytest.mark.parametrize("polls", [0, 1, 6])
+@pytest.mark.parametrize("n", WAIT_SIZES)
+def test_workgroups_that_give_up_leave_a_solved_field(n, polls):
+    """With no poll every workgroup gives up at its first wait; with a few some get
+    further than others. The field is then solved by one workgroup: the oracle's iterates
+    within the rounding that the several-workgroup solve is held to."""
+    from oracle import walls as W
+    from paper_2604_18536_amd import Solver
+    from paper_2604_18536_amd import _lib as L
+    from tests.gpu_util import host, max_rel
+
+    lo, hi = S.channel_box(n)
+    h = S.spacing(n, lo, hi)
+    s = Solver(n, batch=2, nu=0.01, lo=lo, hi=hi, bc="walls", pressure="cg")
+    L.call("ins_cg_set_wait", s._ctx, polls)
+    r = np.stack([S.random_scalar(n, 7), S.random_scalar(n, 8)])
+    for k in (1, 7):
+        s.cg_set(rtol=0.0, maxiter=k, check_every=0)
+        x = host(s.poisson_solve(dev(r)))
+        for b in range(2):
+            xo, ito, rel = W.cg_solve(r[b], h, rtol=0.0, maxiter=k)
+            assert max_rel(x[b], xo) < 1e-11
+        assert s.cg_info()[0] == k
+    s.cg_set(rtol=1e-9, maxiter=5000)
+    s.poisson_solve(dev(r))
+    assert 0.0 < s.cg_info()[1] <= 1e-9
+    s.close()
+
+
+@pytest.mark.parametrize("n,walls", [((70, 63), False), ((42, 35, 20), False), ((42, 35, 20), True)])
+def test_workgroups_that_give_up_on_a_stretched_grid(n, walls):
+    from oracle import stretched as ST
+    from paper_2604_18536_amd import Solver
+    from paper_2604_18536_amd import _lib as L
+    from tests.gpu_util import host, max_rel
+
+    lo, hi = [0.0] * len(n), [2.0] * len(n)
+    faces = [S.tanh_faces(n[a], lo[a], hi[a], 0.8 + 0.2 * a) for a in range(len(n))]
+    s = Solver(n, nu=0.01, lo=lo, hi=hi, bc="walls" if walls else "periodic")
+    for a, f in enumerate(faces):
+        s.set_faces(a, f)
+    L.call("ins_cg_set_wait", s._ctx, 0)
+    o = ST.StretchedGrid(faces, ywalls=walls)
+    r = S.random_scalar(n, 3)
+    for k in (1, 7):
+        s.cg_set(rtol=0.0, maxiter=k, check_every=0)
+        x = host(s.poisson_solve(dev(r)))
+        xo, ito, rel = o.cg_solve(r, rtol=0.0, maxiter=k)
+        assert max_rel(x, xo) < 1e-11 and s.cg_info()[0] == k
+        assert abs(s.cg_info()[1] - rel) <= 1e-10 * rel
+    # waits as long as it takes: the usual solve
+    L.call("ins_cg_set_wait", s._ctx, 1 << 21)
+    x = host(s.poisson_solve(dev(r)))
+    assert max_rel(x, xo) < 1e-11
+    s.close()
