@@ -323,7 +323,8 @@ hipError_t launch_cg_finish(const Grid& g, const double* rb, CgScal* st, hipStre
 // G workgroups per field (0: it does not fit; 1: no exchange between workgroups) of
 // nt threads with c cells each along the last direction, nb[a] blocks of b[a] cells
 // per direction, outboxes of face slots, `fields` fields per launch.
-constexpr int kCgMaxGroups = 64;
+constexpr int kCgMaxGroups = 64, kCgMinCells = 512;
+constexpr int kCgHeadWords = 16;  // a cache line ahead of the exchange, for the count of started workgroups
 constexpr size_t kCgLdsMax = 98304, kCgLdsMulti = 160000;
 struct CgPlan {
     int dim, G, nt, c, face, fields;
@@ -335,7 +336,7 @@ CgPlan cg_plan(const Grid& g, int cus);
 // Polls (about 1 us each) before a workgroup's wait for the others gives up.
 constexpr unsigned kCgSpin = 1u << 21;
 // From r = b (x_0 = 0) and the partial sums rb0 of b.b: x and st of every field.
-// exch: P.words() * P.fields words; p, q: scratch fields (all three unused when
+// exch: kCgHeadWords + P.words() * P.fields words; p, q: scratch fields (all three unused when
 // P.G == 1). r is overwritten where a field is solved again alone.
 hipError_t launch_cg_solve(const Grid& g, const CgPlan& P, double* r, double* x, double* p, double* q, const double* rb0,
                            CgScal* st, void* exch, double rtol2, int maxiter, unsigned spin, hipStream_t s);

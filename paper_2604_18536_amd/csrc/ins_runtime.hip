@@ -509,12 +509,13 @@ void upload_gen_metrics(ins_ctx c) {
     c->wsum = vol;
 }
 
-// Plan and exchange buffer of the single-launch solve (it depends on the sizes alone).
+// Plan and exchange buffer of the single-launch solve (its split depends on the sizes alone,
+// its fields per launch on the batch too).
 void setup_cg_plan(ins_ctx c) {
     int cus = 0;
     hip_check(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, c->device), "hipDeviceGetAttribute");
     c->cg_pl = ins::cg_plan(c->g, cus);
-    if (c->cg_pl.G > 1) c->cg_exch = c->alloc(c->cg_pl.words() * c->cg_pl.fields * sizeof(unsigned long long));
+    if (c->cg_pl.G > 1) c->cg_exch = c->alloc((ins::kCgHeadWords + c->cg_pl.words() * c->cg_pl.fields) * sizeof(unsigned long long));
 }
 
 // Switch a context to the stretched-grid operators (irreversible): the CG

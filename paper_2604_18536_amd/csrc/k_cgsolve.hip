@@ -29,11 +29,19 @@
 // are rewritten in iteration k + 2, after the sums of iteration k + 1, which every
 // reader of the old values has entered by then.
 //
-// All workgroups of a launch have to be resident together. The launch is
-// cooperative, and the plan uses at most a quarter of the workgroups the chip
-// holds, so that launches from the process's four hardware queues fit side by
-// side (a cooperative launch recorded into a graph replays as a plain one). That
-// says nothing of other processes on the same GPU, so every wait is bounded: past
+// The fields of a batch run side by side, as many per launch as the chip holds
+// (128^2, us per iteration for 1 / 16 / 256 fields: 2.7 / 3.5 / 55; one field after
+// another 2.75 / 44 / 705; the two-kernel iteration 12 / 14 / 93). The workgroups
+// of a field have to be resident together. The launch is cooperative, which sees to
+// that; one recorded into a graph replays as a plain one, and there workgroups take
+// their field and block in the order in which they start (`ordered`). Those that run then form
+// whole fields, and a launch has at most one field that waits for workgroups still to
+// start, with at most kCgMaxGroups - 1 = 63 of them on the chip: launches on four
+// hardware queues keep 252 workgroups waiting, fewer than there are CUs, so the next
+// one to start always finds room. (Their order of start places neighbouring blocks
+// worse: 8 fields of 41 x 40 x 40 9.5 us per iteration instead of 9.0, 64 of 128^2
+// 15.7 instead of 13.7.) Neither
+// says anything of other processes on the same GPU, so every wait is bounded: past
 // the bound a workgroup marks its field (CgScal::failed) and leaves, the others
 // follow, and k_cg_alone, launched behind every such solve, solves a marked field
 // again from r_0 with one workgroup, which waits for nobody. The caller gets a
@@ -172,7 +180,7 @@ template <int NT, int C, int DIM, bool MULTI>
 __global__ __launch_bounds__(NT, 2) void k_cg_solve(Grid g, CgPlan P, const double* __restrict__ r0,
                                                   double* __restrict__ x, const double* __restrict__ rb0,
                                                   CgScal* __restrict__ st, u64* __restrict__ ex, int field0,
-                                                  double rtol2, int maxiter, unsigned spin) {
+                                                  double rtol2, int maxiter, unsigned spin, int ordered) {
     // p on the block plus halo, the table of the last direction, (MULTI) q on the block
     extern __shared__ double pl[];
     __shared__ double sh[NT / 64][4], tot[4];
@@ -180,9 +188,17 @@ __global__ __launch_bounds__(NT, 2) void k_cg_solve(Grid g, CgPlan P, const doub
     constexpr int NW = NT / 64, HALO = cg_halo(C);
     constexpr int M = DIM - 1;  // the last direction
     const int tid = threadIdx.x;
-    const int fs = blockIdx.x / P.G;  // field of this launch
+    int id = blockIdx.x;
+    if constexpr (MULTI)
+        if (ordered) {  // by order of start; ex[0]: workgroups of this launch that have started
+            __shared__ unsigned started;
+            if (tid == 0) started = atomicAdd(reinterpret_cast<unsigned*>(ex), 1u);
+            __syncthreads();
+            id = __builtin_amdgcn_readfirstlane(started);
+        }
+    const int fs = id / P.G;  // field of this launch
     const int f = field0 + fs;
-    const int wg = blockIdx.x - fs * P.G;
+    const int wg = id - fs * P.G;
     const int n[3] = {g.nx, g.ny, g.nz};
     const int bc[3] = {wg % P.nb[0], (wg / P.nb[0]) % P.nb[1], wg / (P.nb[0] * P.nb[1])};
     int o[3], e[3];  // origin and extent of the block
@@ -206,11 +222,12 @@ __global__ __launch_bounds__(NT, 2) void k_cg_solve(Grid g, CgPlan P, const doub
         td[i] = wall ? 0.0 : met_id(g, M, n[M], o[M] + i - 1);
     }
     // (a workgroup that starts after another has given up need not wait its own bound out)
-    if (tid == 0) lost = MULTI && __hip_atomic_load(&st[f].failed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if constexpr (MULTI)
+        if (tid == 0) lost = __hip_atomic_load(&st[f].failed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 
     // words of this field, for even and odd iterations: P.G * 2 * DIM outboxes of
     // P.face slots, then the four partial sums of each workgroup
-    const Rsrc fx = __builtin_amdgcn_make_buffer_rsrc(ex + size_t(fs) * P.words(), 0, int(P.words() * sizeof(u64)), 0x00027000);
+    const Rsrc fx = __builtin_amdgcn_make_buffer_rsrc(ex + kCgHeadWords + size_t(fs) * P.words(), 0, int(P.words() * sizeof(u64)), 0x00027000);
     const unsigned red = P.G * 2 * DIM * P.face * 2;
     const unsigned half = unsigned(P.words() / 2);
     auto outbox = [&](int w, int face) { return unsigned((w * 2 * DIM + face) * P.face * 2); };
@@ -335,7 +352,7 @@ __global__ __launch_bounds__(NT, 2) void k_cg_solve(Grid g, CgPlan P, const doub
     }
     double rr = rr0;
     int k = 0;
-    if (!lost && !cg_stopped(rr0, rr0, 0, rtol2, maxiter)) {
+    if (!(MULTI && lost) && !cg_stopped(rr0, rr0, 0, rtol2, maxiter)) {
 #pragma unroll
         for (int j = 0; j < C; ++j)
             if (j < nc) pl[cell0 + j * sm] = p[j];
@@ -608,7 +625,10 @@ CgPlan cg_plan(const Grid& g, int cus) {
     }
     // several: the fewest cells per thread that a quarter of the chip's room allows
     // (an iteration costs its two sums and C steps of the stencil), among those the
-    // split with the smallest halo
+    // split with the smallest halo, but at least kCgMinCells cells per workgroup (the
+    // smallest halo alone took 54 workgroups for 17^3 and 64 for 128^2, no faster alone
+    // than 9 and 32: 2.9 / 2.8 and 2.75 / 2.75 us per iteration; 256 fields of 128^2
+    // then took 117 us on the whole chip instead of 55, the two-kernel iteration 93)
     for (int c : {2, 4, 8, 10, 20}) {
         CgPlan B{};
         int64_t best = 0;
@@ -620,7 +640,7 @@ CgPlan cg_plan(const Grid& g, int cus) {
             (void)hipGetLastError();
             break;
         }
-        const int gmax = std::min(kCgMaxGroups, per_cu * cus / 4);
+        const int gmax = std::max(2, int(std::min<int64_t>(std::min(kCgMaxGroups, per_cu * cus / 4), g.ncell / kCgMinCells)));
         for (int i = 1; i <= std::min(n[0], gmax); ++i) {
             P.b[0] = (n[0] + i - 1) / i;
             if ((n[0] + P.b[0] - 1) / P.b[0] != i) continue;
@@ -649,7 +669,11 @@ CgPlan cg_plan(const Grid& g, int cus) {
             }
         }
         if (B.G) {
-            B.fields = std::min(g.batch, per_cu * cus / (4 * B.G));
+            if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, cg_kernel(g, B), B.nt, cg_lds(g, B)) != hipSuccess) {
+                (void)hipGetLastError();
+                break;
+            }
+            B.fields = std::max(1, std::min(g.batch, per_cu * cus / B.G));
             return B;
         }
     }
@@ -664,14 +688,19 @@ hipError_t launch_cg_solve(const Grid& g, const CgPlan& P, double* r, double* x,
     const void* kern = cg_kernel(g, P);
     const size_t lds = cg_lds(g, P);
     const int step = P.G == 1 ? g.batch : P.fields;
+    // a launch of one field needs no order; an error here is that of a stream which must
+    // not be used while another one records, and the launch below reports it
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    if (P.fields > 1 && hipStreamIsCapturing(s, &capture) != hipSuccess) (void)hipGetLastError();
+    int ordered = capture != hipStreamCaptureStatusNone;
     for (int f0 = 0; f0 < g.batch; f0 += step) {
         const int nf = std::min(step, g.batch - f0);
-        void* args[] = {&ga, &pa, &r, &x, &rb0, &st, &ex, &f0, &rtol2, &maxiter, &spin};
+        void* args[] = {&ga, &pa, &r, &x, &rb0, &st, &ex, &f0, &rtol2, &maxiter, &spin, &ordered};
         hipError_t e;
         if (P.G == 1) {
             e = hipLaunchKernel(kern, dim3(nf), dim3(P.nt), args, lds, s);
         } else {
-            const int64_t words = int64_t(P.words()) * nf;
+            const int64_t words = kCgHeadWords + int64_t(P.words()) * nf;
             hipLaunchKernelGGL(k_cg_clear, dim3(int((words + kBlock - 1) / kBlock)), dim3(kBlock), 0, s, ex, words);
             e = hipGetLastError();
             if (e != hipSuccess) return e;
