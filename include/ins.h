@@ -65,6 +65,9 @@
  * in ins_set_y_faces, and in the CG pressure solves of large fields, which read their
  * convergence flags every check_every iterations (ins_cg_set; 0 turns it off).
  *
+ * Batches. In solves, steps and pullbacks a field of a batch gets, bit for bit, what it
+ * gets alone.
+ *
  * Aliasing. Outputs must not alias inputs, except where an entry point says
  * so. Outputs are overwritten, never accumulated into.
  *

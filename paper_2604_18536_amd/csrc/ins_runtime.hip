@@ -1276,8 +1276,7 @@ bool setup_fft(ins_ctx c, const std::vector<int>& rx, const std::vector<int>& ry
     // workgroups, each as long as its chain of stages (one solve 27.9 -> 19.4 us;
     // 4 x 256^2 28.4 -> 21.0, 1024^2 45.9 -> 39 us). From 256 workgroups on, more
     // lines (longer runs) are better: 96 x 90 x 84 with a quarter of them 43.8 -> 58 us.
-    // (The batch counts: a field in a large one may differ from the field alone by the
-    // order of an FMA contraction, 1e-17 of a solve.)
+    // (The batch counts; a field's bits do not depend on the choice, see k_fft.hpp.)
     auto most_lines = [](int64_t lines) {
         int m = 16;
         while (m > 2 && lines / m < 256) m /= 2;

@@ -112,11 +112,11 @@ __device__ __forceinline__ void stage_div_rows(const Grid& g, const T* __restric
                 const int l = fdivmod(t, M, rM, m);
                 F r0 = (ux0[j] - uxm[j]) * ihx;
                 F r1 = (ux1[j] - ux0[j]) * ihx;
-                r0 += (uy0[j] - vy0[j]) * ihy;
-                r1 += (uy1[j] - vy1[j]) * ihy;
+                r0 = fma(uy0[j] - vy0[j], ihy, r0);
+                r1 = fma(uy1[j] - vy1[j], ihy, r1);
                 if constexpr (DIM == 3) {
-                    r0 += (uz0[j] - vz0[j]) * ihz;
-                    r1 += (uz1[j] - vz1[j]) * ihz;
+                    r0 = fma(uz0[j] - vz0[j], ihz, r0);
+                    r1 = fma(uz1[j] - vz1[j], ihz, r1);
                 }
                 lds[m * ls + l] = row0 + l < nrows ? C{r0, r1} : C{F(0), F(0)};
             }
@@ -188,8 +188,8 @@ __global__ __launch_bounds__(NTH) void k_fft_x_fwd(Grid g, const T* __restrict__
                     double uz0, uz1, vz0, vz1;
                     ld_pair(wz + rowoff + x0, uz0, uz1);
                     ld_pair(wz + (zm * g.ny + yy) * g.nx + x0, vz0, vz1);
-                    r0 += (uz0 - vz0) * g.ih[2];
-                    r1 += (uz1 - vz1) * g.ih[2];
+                    r0 = fma(uz0 - vz0, g.ih[2], r0);
+                    r1 = fma(uz1 - vz1, g.ih[2], r1);
                 }
                 if constexpr (SRC == 4) {
                     r0 /= sp;
@@ -206,9 +206,11 @@ __global__ __launch_bounds__(NTH) void k_fft_x_fwd(Grid g, const T* __restrict__
                     vy0 *= id;
                     vy1 *= id;
                 }
+                // (no contraction of the products that make r0 and uy0 into the sums)
+                asm("" : "+v"(r0), "+v"(r1), "+v"(uy0), "+v"(uy1), "+v"(vy0), "+v"(vy1));
                 const double iw = g.ym[yy];
-                r0 += (uy0 - vy0) * iw;
-                r1 += (uy1 - vy1) * iw;
+                r0 = fma(uy0 - vy0, iw, r0);
+                r1 = fma(uy1 - vy1, iw, r1);
                 return C{F(r0), F(r1)};
             } else {
                 const T* wb = vel + int64_t(b) * DIM * g.ncell;
@@ -257,7 +259,7 @@ __global__ __launch_bounds__(NTH) void k_fft_x_fwd(Grid g, const T* __restrict__
         const C e = cscale(cadd(zk, zc), F(0.5));
         const C dd = csub(zk, zc);
         const C o = {F(0.5) * dd.y, F(-0.5) * dd.x};
-        spec[int64_t(row) * g.sx + k] = cadd(e, cmul(post[k], o));
+        spec[int64_t(row) * g.sx + k] = cmadd(post[k], o, e);
     }
 }
 
@@ -290,8 +292,10 @@ __device__ __forceinline__ void stage_tangled_rows(const Grid& g, const C* __res
                 const int l = fdivmod(t, M, rM, k);
                 const C xc = cconj(xm[j]);
                 const C e = cadd(xk[j], xc);
-                const C o = cmulc(csub(xk[j], xc), wk[j]);
-                lds[k * ls + l] = row0 + l < nrows ? C{e.x - o.y, e.y + o.x} : C{real_of<C>(0), real_of<C>(0)};
+                // e + i (X[k] - conj X[M-k]) conj(W^k)
+                const C d = csub(xk[j], xc);
+                const C z = cmadd(C{-d.y, d.x}, cconj(wk[j]), e);
+                lds[k * ls + l] = row0 + l < nrows ? z : C{real_of<C>(0), real_of<C>(0)};
             }
         }
     }
@@ -439,7 +443,9 @@ __device__ __forceinline__ void strided_batch(const Grid& g, C* __restrict__ spe
         auto divide = [&](int l, int e, C z) INS_INLINE -> C {
             if (l >= B.nvalid) return z;
             const F sc = (lam.zero && e == 0) ? inv_ncell : -inv_ncell * recip(lam.other + lam_line[e]);
-            return cscale(z, sc);
+            C v = cscale(z, sc);
+            asm("" : "+v"(v.x), "+v"(v.y));  // a product on its own in every instance
+            return v;
         };
         fft_run<-1, VM, NTH, 0, 2, kLineFast, kLineFast>(lds, lnl, ls, P, rt, load, store, divide, &Q);
         fft_inverse_rest<1, VM, NTH, kLineFast>(lds, lnl, ls, Q, rt, store);

@@ -1,5 +1,14 @@
 // Device side of the FFT passes: small DFTs, twiddles, Stockham stages on batches of
 // lines in LDS (see k_fft.hip).
+//
+// A field's bits do not depend on its batch. How many lines a workgroup takes, which
+// instance runs and (2D) whether the row kernels do is chosen with the batch in view, and
+// the compiler contracts a product and a sum of different statements into an FMA in one
+// instance and not in another, or in one copy of an unrolled loop. So wherever a product
+// meets a sum here and in k_fft.hip the FMA is written out, and the 2D kernels
+// (k_rows2d, k_stencil, k_vjp) contract within an expression only. Cost: the inverse
+// strided pass 54.4 -> 57.0 us at 256^3 (its other passes unchanged, a step 2899 -> 2902
+// us), the 64^2 step 61.6 -> 62.4, ten 256^2 steps and their gradient 4045 -> 4075.
 #pragma once
 
 #include "k_common.hpp"
@@ -62,17 +71,17 @@ __device__ __forceinline__ void dft8(C* v) {
     dft4<SIGN>(o0, o1, o2, o3);
     constexpr F r = F(0.7071067811865476);
     // w^1 = (1 + SIGN i)/sqrt2, w^2 = SIGN i, w^3 = (-1 + SIGN i)/sqrt2
-    const C t1 = {r * (o1.x - SIGN * o1.y), r * (o1.y + SIGN * o1.x)};
+    const C t1 = {o1.x - SIGN * o1.y, o1.y + SIGN * o1.x};
     const C t2 = rot<SIGN>(o2);
-    const C t3 = {r * (-o3.x - SIGN * o3.y), r * (-o3.y + SIGN * o3.x)};
+    const C t3 = {-o3.x - SIGN * o3.y, -o3.y + SIGN * o3.x};
     v[0] = cadd(e0, o0);
     v[4] = csub(e0, o0);
-    v[1] = cadd(e1, t1);
-    v[5] = csub(e1, t1);
+    v[1] = C{fma(r, t1.x, e1.x), fma(r, t1.y, e1.y)};
+    v[5] = C{fma(-r, t1.x, e1.x), fma(-r, t1.y, e1.y)};
     v[2] = cadd(e2, t2);
     v[6] = csub(e2, t2);
-    v[3] = cadd(e3, t3);
-    v[7] = csub(e3, t3);
+    v[3] = C{fma(r, t3.x, e3.x), fma(r, t3.y, e3.y)};
+    v[7] = C{fma(-r, t3.x, e3.x), fma(-r, t3.y, e3.y)};
 }
 
 // Odd R: pair x[q] with x[R-q]; X[m] = A_m + SIGN i B_m, X[R-m] = A_m - SIGN i B_m with
@@ -98,10 +107,10 @@ __device__ __forceinline__ void dft_odd(C* v) {
 #pragma unroll
         for (int q = 1; q <= H; ++q) {
             const int j = (q * m) % R;
-            A.x += s[q - 1].x * F(kcos(R, j));
-            A.y += s[q - 1].y * F(kcos(R, j));
-            B.x += d[q - 1].x * F(ksin(R, j));
-            B.y += d[q - 1].y * F(ksin(R, j));
+            A.x = fma(s[q - 1].x, F(kcos(R, j)), A.x);
+            A.y = fma(s[q - 1].y, F(kcos(R, j)), A.y);
+            B.x = fma(d[q - 1].x, F(ksin(R, j)), B.x);
+            B.y = fma(d[q - 1].y, F(ksin(R, j)), B.y);
         }
         const C iB = rot<SIGN>(B);
         v[m] = cadd(A, iB);

@@ -18,6 +18,8 @@
 // written, so the spectra alternate between two buffers, and so do the fields a
 // kernel reads with neighbours and writes. Arithmetic as in the separate kernels
 // (divergence and projection in float64).
+// Contraction within an expression only: the same bits in every kernel (see k_fft.hpp).
+#pragma clang fp contract(on)
 #include "k_fft.hpp"
 
 namespace ins {
@@ -87,8 +89,8 @@ __device__ __forceinline__ void inverse_rows(const Grid& g, const cd* __restrict
                 const int l = fdivmod(t, M, rM, k);
                 const cd xc = cconj(xm[j]);
                 const cd e = cadd(xk[j], xc);
-                const cd o = cmulc(csub(xk[j], xc), wk[j]);
-                line[k * kLsInv + l] = cd{e.x - o.y, e.y + o.x};
+                const cd d = csub(xk[j], xc);
+                line[k * kLsInv + l] = cmadd(cd{-d.y, d.x}, cconj(wk[j]), e);
             }
         }
     }
@@ -131,7 +133,7 @@ __device__ __forceinline__ void forward_rows(const Grid& g, const T* v, const Ff
         const cd e = cscale(cadd(zk, zc), 0.5);
         const cd dd = csub(zk, zc);
         const cd o = {0.5 * dd.y, -0.5 * dd.x};
-        spec[int64_t(y0 + l) * g.sx + k] = cadd(e, cmul(post[k], o));
+        spec[int64_t(y0 + l) * g.sx + k] = cmadd(post[k], o, e);
     }
 }
 

@@ -468,7 +468,8 @@ __global__ __launch_bounds__(TX * TY) void k_stage_vjp_zm(Grid g, const T* __res
                         T uv = hw[s][c];
                         if constexpr (PROJ_U) uv = T(double(hw[s][c]) - (hp[s][c + 1] - hp[s][0]) * g.ih[c]);
                         T fv = cb * hy[s][c];
-                        if constexpr (HAS_W) fv += cw * T(double(hu[s][c]) - (hqv[s][c + 1] - hqv[s][0]) * g.ih[c]);
+                        // (the FMA written out: several copies of this body, the same bits)
+                        if constexpr (HAS_W) fv = fma(cw, T(double(hu[s][c]) - (hqv[s][c + 1] - hqv[s][0]) * g.ih[c]), fv);
                         su[c * HP + hq[s]] = uv;
                         sf[c * HP + hq[s]] = fv;
                     }
@@ -544,7 +545,7 @@ __global__ __launch_bounds__(TX * TY) void k_stage_vjp_zm(Grid g, const T* __res
                     else
                         pu[s][c] = wb[c * nc + j];
                     T fv = cb * yb[c * nc + j];
-                    if constexpr (HAS_W) fv += cw * T(double(ub[c * nc + j]) - (qb[jp[c]] - qc) * g.ih[c]);
+                    if constexpr (HAS_W) fv = fma(cw, T(double(ub[c * nc + j]) - (qb[jp[c]] - qc) * g.ih[c]), fv);
                     pf[s][c] = fv;
                 }
             }

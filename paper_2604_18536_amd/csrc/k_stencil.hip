@@ -6,6 +6,8 @@
 // all components of a cell in one thread so each neighbour load is shared by
 // the three component stencils, tiles of 64 x 4 cells ordered per XCD so halo
 // rows are reused from the L2 of the XCD that loaded them.
+// Contraction within an expression only: the same bits in every kernel (see k_fft.hpp).
+#pragma clang fp contract(on)
 #include "k_common.hpp"
 
 namespace ins {

@@ -14,6 +14,8 @@
 // u^g[J]. (The printed eight-term pullback of App. B places the primal factor
 // of four of its terms one cell off; this form is derived from the forward
 // kernel instead.)
+// Contraction within an expression only: the same bits in every kernel (see k_fft.hpp).
+#pragma clang fp contract(on)
 #include "k_common.hpp"
 
 namespace ins {

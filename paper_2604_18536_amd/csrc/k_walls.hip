@@ -759,9 +759,10 @@ __global__ __launch_bounds__(kBlock) void k_wall_stage_vjp_zm(Grid g, const T* _
                     if constexpr (PROJ_U) uv = T(double(rw[s][c]) - (rp[s][c + 1] - rp[s][0]) * gs);
                     T fv = cb * ry[s][c];
                     if constexpr (HAS_W) {
-                        const double dq = rq[s][c + 1] - rq[s][0];
-                        const double og = c == 1 ? dq : hw[s] * dq * g.ih[c];
-                        fv += cw * T(double(ru_[s][c]) - og);
+                        // (FMAs written out: this body is compiled in several copies, whose
+                        // bits must not depend on where a chunk of planes starts)
+                        const double dq = rq[s][c + 1] - rq[s][0], uq = double(ru_[s][c]);
+                        fv = fma(cw, T(c == 1 ? uq - dq : fma(-(hw[s] * dq), g.ih[c], uq)), fv);
                     }
                     const bool neg = c != 1 && hghost[s];
                     const bool zero = c == 1 && !hunk[s];
