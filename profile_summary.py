@@ -26,6 +26,7 @@ import csv
 import hashlib
 import json
 import os
+import re
 import sys
 from collections import defaultdict
 
@@ -35,39 +36,53 @@ CSRC = os.path.join(ROOT, "paper_2604_18536_amd", "csrc")
 # template instance (prefix of the demangled name) -> (variant names in dispatch order, source files),
 # per workload: the same kernel serves different steps on the periodic grid and on the channel
 # (the strided FFT pass is y there, z here), so channel records carry a "channel:" prefix.
-_WALL = ["k_walls.hip", "k_common.hpp", "ins_internal.hpp"]
+# A record's hash also covers every local header that the source files include.
 VARIANT_ORDERS = {
     "periodic": {
-        "void ins::k_stage_zm<double, true, 64, 8, double, false, 1>": (["stage_rec"], ["k_stage3d.hip", "k_common.hpp"]),
-        "void ins::k_stage_zm<double, true, 64, 8, double, false, 2>": (["stage_last"], ["k_stage3d.hip", "k_common.hpp"]),
-        "void ins::k_stage_zm<double, true, 64, 8, double, true, 3>": (["stage_yw"], ["k_stage3d.hip", "k_common.hpp"]),
-        "void ins::k_stage_zm<double, false,": (["stage_first_rec"], ["k_stage3d.hip", "k_common.hpp"]),
-        "void ins::k_fft_x_fwd<double, 3, 0,": (["fft_x_fwd_div"], ["k_fft.hip", "k_common.hpp"]),
-        "void ins::k_fft_strided<0,": (["fft_y_fwd"], ["k_fft.hip", "k_common.hpp"]),
-        "void ins::k_fft_strided<2,": (["fft_z_solve"], ["k_fft.hip", "k_common.hpp"]),
-        "void ins::k_fft_strided<1,": (["fft_y_inv"], ["k_fft.hip", "k_common.hpp"]),
-        "void ins::k_fft_x_inv<": (["fft_x_inv"], ["k_fft.hip", "k_common.hpp"]),
-        "void ins::k_apply_projection<double, 3,": (["apply_projection"], ["k_stencil.hip", "k_common.hpp"]),
+        "void ins::k_stage_zm<double, true, 64, 8, double, false, 1>": (["stage_rec"], ["k_stage3d.hip"]),
+        "void ins::k_stage_zm<double, true, 64, 8, double, false, 2>": (["stage_last"], ["k_stage3d.hip"]),
+        "void ins::k_stage_zm<double, true, 64, 8, double, true, 3>": (["stage_yw"], ["k_stage3d.hip"]),
+        "void ins::k_stage_zm<double, false,": (["stage_first_rec"], ["k_stage3d.hip"]),
+        "void ins::k_fft_x_fwd<double, 3, 0,": (["fft_x_fwd_div"], ["k_fft.hip"]),
+        "void ins::k_fft_strided<0,": (["fft_y_fwd"], ["k_fft.hip"]),
+        "void ins::k_fft_strided<2,": (["fft_z_solve"], ["k_fft.hip"]),
+        "void ins::k_fft_strided<1,": (["fft_y_inv"], ["k_fft.hip"]),
+        "void ins::k_fft_x_inv<": (["fft_x_inv"], ["k_fft.hip"]),
+        "void ins::k_apply_projection<double, 3,": (["apply_projection"], ["k_stencil.hip"]),
     },
     # channel, direct pressure solve (FFTs along x and z, tridiagonal solves along y)
     "channel": {
-        "void ins::k_wall_stage_zm<double, true,": (["channel:stage_rec", "channel:stage_yw", "channel:stage_last"], _WALL),
-        "void ins::k_wall_stage_zm<double, false,": (["channel:stage_first_rec"], _WALL),
-        "void ins::k_fft_x_fwd<double, 3, 3,": (["channel:fft_x_fwd_div"], ["k_fft.hip", "k_common.hpp"]),
-        "void ins::k_fft_strided<0,": (["channel:fft_z_fwd"], ["k_fft.hip", "k_common.hpp"]),
-        "void ins::k_channel_ysolve<": (["channel:channel_ysolve"], ["k_chsolve.hip", "k_common.hpp"]),
-        "void ins::k_fft_strided<1,": (["channel:fft_z_inv"], ["k_fft.hip", "k_common.hpp"]),
-        "void ins::k_fft_x_inv<": (["channel:fft_x_inv"], ["k_fft.hip", "k_common.hpp"]),
-        "void ins::k_wall_project<double, 3, false>": (["channel:wall_projection"], _WALL),
+        "void ins::k_wall_stage_zm<double, true,": (["channel:stage_rec", "channel:stage_yw", "channel:stage_last"], ["k_walls.hip"]),
+        "void ins::k_wall_stage_zm<double, false,": (["channel:stage_first_rec"], ["k_walls.hip"]),
+        "void ins::k_fft_x_fwd<double, 3, 3,": (["channel:fft_x_fwd_div"], ["k_fft.hip"]),
+        "void ins::k_fft_strided<0,": (["channel:fft_z_fwd"], ["k_fft.hip"]),
+        "void ins::k_channel_ysolve<": (["channel:channel_ysolve"], ["k_chsolve.hip"]),
+        "void ins::k_fft_strided<1,": (["channel:fft_z_inv"], ["k_fft.hip"]),
+        "void ins::k_fft_x_inv<": (["channel:fft_x_inv"], ["k_fft.hip"]),
+        "void ins::k_wall_project<double, 3, false>": (["channel:wall_projection"], ["k_walls.hip"]),
     },
     # channel, conjugate-gradient pressure solve: the two kernels of an iteration
     "channel_cg": {
-        "ins::k_cg_apply3": (["channel:cg_apply"], _WALL),
-        "void ins::k_cg_update<512, 3>": (["channel:cg_update"], _WALL),
+        "ins::k_cg_apply3": (["channel:cg_apply"], ["k_walls.hip"]),
+        "void ins::k_cg_update<512, 3>": (["channel:cg_update"], ["k_walls.hip"]),
     },
 }
 VARIANT_ORDER = VARIANT_ORDERS["periodic"]
 COPY = "ins::k_stream_copy"
+
+
+def with_headers(files):
+    """files and the local headers they include, directly or through one another, in first-seen order."""
+    out = []
+    todo = list(files)
+    while todo:
+        f = todo.pop(0)
+        if f in out:
+            continue
+        out.append(f)
+        with open(os.path.join(CSRC, f)) as fh:
+            todo += [os.path.basename(h) for h in re.findall(r'#include "([^"]+)"', fh.read())]
+    return out
 
 
 def source_hash(files):
@@ -138,7 +153,8 @@ def traffic(fetch_csv, write_csv, out_md, command, copy_bytes=None, order=None, 
     jpath = os.path.join(ROOT, "profiles", "traffic.json")
     if os.path.exists(jpath):
         rec = json.load(open(jpath))
-    for inst, (variants, srcs) in order.items():
+    for inst, (variants, files) in order.items():
+        srcs = with_headers(files)
         # a key is the demangled name or, for kernels templated on the FFT plan, its prefix
         names = [k for k in f if k == inst or (inst.endswith((",", "<")) and k.startswith(inst))]
         if not names:
