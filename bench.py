@@ -5,17 +5,18 @@ nu = 1/1600, dt = 1e-3, seeded solenoidal initial field with
 E(k) ~ k^4 exp(-2 (k/4)^2) and unit kinetic energy.
 
 `value` is the float64 forward step rate in Mcell-updates/s (one cell update =
-one full RK4 step of one cell; inputs resident in HBM). The same line reports
-the float64 forward+adjoint rate, the FP32-stencil mode (float32 fields,
-float64 divergence/Poisson/projection), Wray's low-storage RK3 step (modes
-*_wray3: three stages and solves per step), forward+adjoint with the stage
-inputs kept from the forward instead of recomputed (modes *_adj_kept), the
-HBM-roofline fraction of each
-step and of the dominant kernel (per-kernel durations from HIP events recorded
-on the library's stream), and the float64 CPU oracle timed on a bounded
-sample of the same workload.
+one full RK4 step of one cell; inputs resident in HBM). The line also holds the
+rates of the other modes: float64 forward+adjoint, the FP32-stencil mode
+(float32 fields, float64 divergence/Poisson/projection), Wray's low-storage RK3
+step (modes *_wray3: three stages and solves per step), forward+adjoint with the
+stage inputs kept from the forward instead of recomputed (modes *_adj_kept); the
+HBM roofline of the dominant kernel (durations from HIP events recorded on the
+library's stream); and the float64 CPU oracle timed on a bounded sample of the
+same workload. --record FILE writes everything that was measured: each mode's
+and kernel's bytes and times, the larger grids, the channel, the LES and the
+precision study.
 
-Usage: python bench.py [--gpus 1] [--steps K] [--warmup W] [--n 256] [--no-cpu]
+Usage: python bench.py [--gpus 1] [--steps K] [--warmup W] [--n 256] [--no-cpu] [--record FILE]
 """
 from __future__ import annotations
 
@@ -514,6 +515,29 @@ def cpu_baseline(n, nu, dt, u0_np, budget_s=30.0):
     }
 
 
+# The printed line: what is read of a run's output is its last few thousand characters.
+LINE_KEYS = ("metric", "value", "unit", "n_gpus", "steps", "warmup", "ms_per_step", "higher_is_better", "scaling",
+             "vs_baseline", "dtype", "data", "config", "roofline", "stream_copy_gbs")
+
+
+def headline(record):
+    """The line of a run: the contract's keys, the rate of every mode and of the CPU oracle."""
+    line = {k: record[k] for k in LINE_KEYS}
+    line["mcell_per_s"] = {m: r["mcell_per_s"] for m, r in record["modes"].items()}
+    cpu = record.get("cpu_baseline")
+    line["cpu_baseline"] = {k: cpu[k] for k in ("value", "unit", "cores", "kind")} if cpu else None
+    return line
+
+
+def report(record, path):
+    """Print the line; write the whole record (per-kernel tables, other workloads) to `path` if given."""
+    if path:
+        with open(path, "w") as fh:
+            json.dump(record, fh, indent=1)
+            fh.write("\n")
+    print(json.dumps(headline(record)), flush=True)
+
+
 def main():
     ap = argparse.ArgumentParser()
     ap.add_argument("--gpus", type=int, default=1)
@@ -527,6 +551,7 @@ def main():
     ap.add_argument("--no-channel", action="store_true", help="skip the channel (wall-bounded) timing")
     ap.add_argument("--modes", default=None)
     ap.add_argument("--sizes", default="512,840", help="larger grids for the per-kernel table ('' to skip)")
+    ap.add_argument("--record", default=None, help="file for the whole record (tables per kernel and workload)")
     ap.add_argument("--no-precision", action="store_true", help="skip the 256^3 precision study")
     args = ap.parse_args()
     if args.config in ("channel256", "channel_dns", "channel_vk"):
@@ -656,7 +681,7 @@ def main():
         "modes": modes,
         "kernels": kernels,
     }
-    print(json.dumps(line))
+    report(line, args.record)
 
 
 def channel_main(args):
@@ -695,7 +720,7 @@ def channel_main(args):
         "modes": ch["modes"],
         "kernels": ch["kernels"],
     }
-    print(json.dumps(line))
+    report(line, args.record)
 
 
 if __name__ == "__main__":
