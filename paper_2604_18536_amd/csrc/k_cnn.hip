@@ -323,9 +323,9 @@ __global__ __launch_bounds__(kBlock) void k_conv_t(Grid g, const u16* __restrict
             for (int n = 0; n < 3; ++n) old[n] = fout[(int64_t(b) * 3 + n) * vol + (ok ? c - bcell : 0)];
         }
     };
-    // the weight operands of tap column tyx (tz = 0, 1, 2; 32 input channels), fetched PF
-    // columns ahead: with one tile of outputs all of them, once per workgroup
-    constexpr int PF = NT == 1 ? 9 : (BZ == 2 ? 2 : 1);
+    // the weight operands of tap column tyx (tz = 0, 1, 2; 32 input channels), fetched one
+    // column ahead; with one tile of outputs all of them, once per workgroup
+    constexpr int PF = NT == 1 ? 9 : 1;
     bf16x8 bn[PF][3][NT];
     auto fetch_w = [&](int tyx) __attribute__((always_inline)) {
 #pragma unroll

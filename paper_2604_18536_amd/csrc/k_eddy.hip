@@ -512,12 +512,10 @@ hipError_t launch_eddy_stage_zm(const Grid& g, const T* w, const double* p, bool
     } while (0)
     if (wprev)
         INS_ESZM(true, true, 3);
-    else if (!proj && pt == 3)
-        INS_ESZM(false, false, 3);
+    else if (pt == 3)
+        return hipErrorInvalidValue;  // no schedule reads both u0 and y otherwise
     else if (!proj)
         INS_ESZM(false, false, 1);
-    else if (pt == 3)
-        INS_ESZM(true, false, 3);
     else if (pt == 2)
         INS_ESZM(true, false, 2);
     else
