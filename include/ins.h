@@ -140,9 +140,9 @@ typedef struct {
  * nu >= 0 is the kinematic viscosity of the diffusion term. Allocates the
  * forward workspace: stage registers (3 velocity fields), pressure, the half
  * spectrum (periodic grid, and the channel when its direct solver applies) and
- * three CG pressure-point fields and the CG's exchange buffer (channel; 8 to 40 bytes
- * per cell of the fields that the chip solves side by side, so tens of megabytes at
- * most). */
+ * three CG pressure-point fields (channel; one where a field takes one workgroup) and the
+ * CG's exchange buffer (channel; tens of bytes per cell of the fields that the chip solves
+ * side by side, at most about 50 MB). */
 ins_status ins_create(const ins_grid* grid, ins_bc bc, double nu, ins_dtype dtype, ins_ctx* out);
 ins_status ins_destroy(ins_ctx ctx);
 /* stream: a hipStream_t (NULL = null stream). */

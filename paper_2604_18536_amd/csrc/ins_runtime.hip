@@ -510,11 +510,15 @@ void upload_gen_metrics(ins_ctx c) {
 }
 
 // Plan and exchange buffer of the single-launch solve (its split depends on the sizes alone,
-// its fields per launch on the batch too).
+// its fields per launch on the batch too); the search directions of the two-kernel
+// iteration, which are the scratch of the several-workgroup solve as well (one workgroup
+// needs neither).
 void setup_cg_plan(ins_ctx c) {
     int cus = 0;
     hip_check(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, c->device), "hipDeviceGetAttribute");
     c->cg_pl = ins::cg_plan(c->g, cus);
+    if (c->cg_pl.G != 1)
+        for (double*& p : c->cg_p) p = static_cast<double*>(c->alloc(c->scal_bytes()));
     if (c->cg_pl.G > 1) c->cg_exch = c->alloc((ins::kCgHeadWords + c->cg_pl.words() * c->cg_pl.fields) * sizeof(unsigned long long));
 }
 
@@ -526,8 +530,6 @@ void enter_gen(ins_ctx c) {
         const ins::Grid& g = c->g;
         const size_t sb = c->scal_bytes();
         c->cg_r = static_cast<double*>(c->alloc(sb));
-        c->cg_p[0] = static_cast<double*>(c->alloc(sb));
-        c->cg_p[1] = static_cast<double*>(c->alloc(sb));
         c->cg_part = static_cast<double*>(c->alloc(5 * size_t(ins::cg_blocks(g)) * g.batch * sizeof(double)));
         c->cg_st = static_cast<ins::CgScal*>(c->alloc(size_t(g.batch) * sizeof(ins::CgScal)));
         hip_check(hipMemset(c->cg_st, 0, size_t(g.batch) * sizeof(ins::CgScal)), "hipMemset");
@@ -732,7 +734,6 @@ constexpr int kW1 = 0, kB1 = 2592, kW2 = 2624, kB2 = 30272, kW3 = 30304, kB3 = 3
 void closure_alloc_common(ins_ctx c) {
     if (c->clos_common) return;
     c->mclos = c->alloc(c->vel_bytes());
-    c->ui = c->alloc(c->vel_bytes());
     c->fbar = c->alloc(c->vel_bytes());
     c->clos_common = true;
 }
@@ -770,6 +771,7 @@ void eddy_alloc(ins_ctx c) {
     const int d = c->g.dim;
     c->eddy_nu = c->alloc(n * es);
     c->eddy_P = c->alloc(n * es * size_t(d * (d + 1) / 2));
+    c->ui = c->alloc(c->vel_bytes());
     closure_alloc_common(c);
 }
 
@@ -1420,8 +1422,6 @@ ins_status ins_create(const ins_grid* grid, ins_bc bc, double nu, ins_dtype dtyp
             // channel grid: CG workspace instead of FFT plans and spectrum
             const size_t sb = c->scal_bytes();
             c->cg_r = static_cast<double*>(c->alloc(sb));
-            c->cg_p[0] = static_cast<double*>(c->alloc(sb));
-            c->cg_p[1] = static_cast<double*>(c->alloc(sb));
             c->cg_part = static_cast<double*>(c->alloc(5 * size_t(ins::cg_blocks(g)) * g.batch * sizeof(double)));
             c->cg_st = static_cast<ins::CgScal*>(c->alloc(size_t(g.batch) * sizeof(ins::CgScal)));
             c->d_ym = static_cast<double*>(c->alloc(5 * size_t(g.ny + 2) * sizeof(double)));
