@@ -586,8 +586,11 @@ const void* cg_kernel(const Grid& g, const CgPlan& P) {
     switch (P.c) {
         case 2: return INS_CGK(512, 2, true);
         case 4: return INS_CGK(512, 4, true);
+        case 6: return INS_CGK(512, 6, true);
         case 8: return INS_CGK(512, 8, true);
         case 10: return INS_CGK(512, 10, true);
+        case 12: return INS_CGK(512, 12, true);
+        case 16: return INS_CGK(512, 16, true);
         default: return INS_CGK(512, 20, true);
     }
 #undef INS_CGK
@@ -624,12 +627,15 @@ CgPlan cg_plan(const Grid& g, int cus) {
         if (cg_threads(P) <= nt && cg_lds(g, P) <= kCgLdsMax) return P;
     }
     // several: the fewest cells per thread that a quarter of the chip's room allows
-    // (an iteration costs its two sums and C steps of the stencil), among those the
-    // split with the smallest halo, but at least kCgMinCells cells per workgroup (the
+    // (an iteration costs its two sums and C steps of the stencil): an even number up to 12,
+    // where the table still fits the registers, then 16 and 20 with the table in LDS, which
+    // holds no more (p with its halo and q of 512 x 24 cells are 200 KB). us per
+    // iteration 2.7 (2 cells) 4.0 (4) 4.7 (6) 5.6 (8) 6.0 (10) 6.9 (12) 7.7 (16) 10 (20).
+    // Among the splits with that many cells the one with the smallest halo, but at least kCgMinCells cells per workgroup (the
     // smallest halo alone took 54 workgroups for 17^3 and 64 for 128^2, no faster alone
     // than 9 and 32: 2.9 / 2.8 and 2.75 / 2.75 us per iteration; 256 fields of 128^2
     // then took 117 us on the whole chip instead of 55, the two-kernel iteration 93)
-    for (int c : {2, 4, 8, 10, 20}) {
+    for (int c : {2, 4, 6, 8, 10, 12, 16, 20}) {
         CgPlan B{};
         int64_t best = 0;
         P.nt = 512;

@@ -37,16 +37,17 @@ def test_a_residual_that_is_not_a_number_is_reported(n):
     s.close()
 
 
-# sizes of 2, 4, 8, 10 and 20 cells per thread (a 2D channel, 3D channels)
-WAIT_SIZES = [(96, 77), (24, 20, 12), (50, 49, 47), (66, 61, 50), (66, 81, 48), (79, 77, 80)]
+# 2 and 6 cells per thread in 2D; 2, 4, 6, 8, 10, 12, 16 and 20 in 3D
+WAIT_SIZES = [(96, 77), (400, 400), (24, 20, 12), (50, 49, 47), (53, 52, 50), (66, 61, 50), (66, 81, 48), (71, 70, 70),
+              (73, 72, 72), (79, 77, 80)]
 
 
-@pytest.mark.parametrize("polls", [0, 1, 6])
+@pytest.mark.parametrize("polls", [0, 1, 6, 1 << 21])
 @pytest.mark.parametrize("n", WAIT_SIZES)
 def test_workgroups_that_give_up_leave_a_solved_field(n, polls):
     """With no poll every workgroup gives up at its first wait; with a few some get
     further than others. The field is then solved by one workgroup: the oracle's iterates
-    within the rounding that the several-workgroup solve is held to."""
+    within the rounding that the several-workgroup solve (with polls enough) is held to."""
     from oracle import walls as W
     from paper_2604_18536_amd import Solver
     from paper_2604_18536_amd import _lib as L
