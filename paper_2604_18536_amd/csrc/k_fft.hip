@@ -199,18 +199,15 @@ __global__ __launch_bounds__(NTH) void k_fft_x_fwd(Grid g, const T* __restrict__
                 double uy0 = 0.0, uy1 = 0.0, vy0 = 0.0, vy1 = 0.0;
                 if (yy < g.ny - 1) ld_pair(wy + rowoff + x0, uy0, uy1);
                 if (yy > 0) ld_pair(wy + rowoff - g.nx + x0, vy0, vy1);
+                double dy0 = uy0 - vy0, dy1 = uy1 - vy1;
                 if constexpr (SRC == 4) {
                     const double iu = g.ym[S + yy + 1], id = g.ym[S + yy];  // 1 / d_j, 1 / d_{j-1}
-                    uy0 *= iu;
-                    uy1 *= iu;
-                    vy0 *= id;
-                    vy1 *= id;
+                    dy0 = fma(uy0, iu, -(vy0 * id));
+                    dy1 = fma(uy1, iu, -(vy1 * id));
                 }
-                // (no contraction of the products that make r0 and uy0 into the sums)
-                asm("" : "+v"(r0), "+v"(r1), "+v"(uy0), "+v"(uy1), "+v"(vy0), "+v"(vy1));
                 const double iw = g.ym[yy];
-                r0 = fma(uy0 - vy0, iw, r0);
-                r1 = fma(uy1 - vy1, iw, r1);
+                r0 = fma(dy0, iw, r0);
+                r1 = fma(dy1, iw, r1);
                 return C{F(r0), F(r1)};
             } else {
                 const T* wb = vel + int64_t(b) * DIM * g.ncell;
