@@ -44,14 +44,14 @@ __device__ __forceinline__ Nb make_nb(const Grid& g, int x, int y, int z) {
 __device__ __forceinline__ cd cadd(cd a, cd b) { return {a.x + b.x, a.y + b.y}; }
 __device__ __forceinline__ cd csub(cd a, cd b) { return {a.x - b.x, a.y - b.y}; }
 __device__ __forceinline__ cd cmul(cd a, cd b) { return {fma(a.x, b.x, -(a.y * b.y)), fma(a.x, b.y, a.y * b.x)}; }
-__device__ __forceinline__ cd cmulc(cd a, cd b) { return {fma(a.x, b.x, a.y * b.y), fma(a.y, b.x, -(a.x * b.y))}; }  // a*conj(b)
+__device__ __forceinline__ cd cmulc(cd a, cd b) { return {fma(a.y, b.y, a.x * b.x), fma(-a.x, b.y, a.y * b.x)}; }  // a*conj(b)
 __device__ __forceinline__ cd cscale(cd a, double s) { return {a.x * s, a.y * s}; }
 __device__ __forceinline__ cd cconj(cd a) { return {a.x, -a.y}; }
 __device__ __forceinline__ cd cmadd(cd a, cd b, cd c) { return {fma(a.x, b.x, fma(-a.y, b.y, c.x)), fma(a.x, b.y, fma(a.y, b.x, c.y))}; }  // a*b + c
 __device__ __forceinline__ cf cadd(cf a, cf b) { return {a.x + b.x, a.y + b.y}; }
 __device__ __forceinline__ cf csub(cf a, cf b) { return {a.x - b.x, a.y - b.y}; }
 __device__ __forceinline__ cf cmul(cf a, cf b) { return {fmaf(a.x, b.x, -(a.y * b.y)), fmaf(a.x, b.y, a.y * b.x)}; }
-__device__ __forceinline__ cf cmulc(cf a, cf b) { return {fmaf(a.x, b.x, a.y * b.y), fmaf(a.y, b.x, -(a.x * b.y))}; }  // a*conj(b)
+__device__ __forceinline__ cf cmulc(cf a, cf b) { return {fmaf(a.y, b.y, a.x * b.x), fmaf(-a.x, b.y, a.y * b.x)}; }  // a*conj(b)
 __device__ __forceinline__ cf cmadd(cf a, cf b, cf c) { return {fmaf(a.x, b.x, fmaf(-a.y, b.y, c.x)), fmaf(a.x, b.y, fmaf(a.y, b.x, c.y))}; }
 __device__ __forceinline__ cf cscale(cf a, float s) { return {a.x * s, a.y * s}; }
 __device__ __forceinline__ cf cconj(cf a) { return {a.x, -a.y}; }

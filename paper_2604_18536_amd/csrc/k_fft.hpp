@@ -7,8 +7,9 @@
 // instance and not in another, or in one copy of an unrolled loop. So wherever a product
 // meets a sum here and in k_fft.hip the FMA is written out, and the 2D kernels
 // (k_rows2d, k_stencil, k_vjp) contract within an expression only. Cost: the inverse
-// strided pass 54.4 -> 57.0 us at 256^3 (its other passes unchanged, a step 2899 -> 2902
-// us), the 64^2 step 61.6 -> 62.4, ten 256^2 steps and their gradient 4045 -> 4075.
+// strided pass 54.4 -> 56.3 us at 256^3 (its other passes unchanged or 1 % faster, a step
+// 2912 -> 2911 us), the 64^2 step 61.7 -> 62.9, ten 256^2 steps and their gradient 4045 -> 4085.
+// (With the other product of cmulc in the FMA the inverse strided pass takes 57.0 us.)
 #pragma once
 
 #include "k_common.hpp"

@@ -11,8 +11,8 @@
 // LDS phases (load, 2-4 FFT stages, stencil, 2-4 FFT stages, store: 6 us at 64^2,
 // about 12 at 256^2) on 16-64 of the 256 CUs; the data is 0.1-4 MB. The rows
 // recomputed here (two inverse transforms per row instead of one, 5/4 of the stencil)
-// cost less than the launches they replace. 64^2 step 75 -> 62 us, ten 256^2 steps and
-// their gradient 4291 -> 4075 us.
+// cost less than the launches they replace. 64^2 step 75 -> 63 us, ten 256^2 steps and
+// their gradient 4291 -> 4085 us.
 //
 // The solved spectrum is read with its neighbours' rows while the next one is
 // written, so the spectra alternate between two buffers, and so do the fields a
@@ -356,9 +356,9 @@ int rows_blocks(const Grid& g) { return (g.ny + kRB - 1) / kRB * g.batch; }
 // one per CU (a second round costs what the launches saved), and its rows short (one
 // workgroup's phases grow with them, the separate kernels spread them over the chip).
 // Step / pullback in us here against the separate kernels:
-//   float64  64^2 62 / 111 vs 75 / 137, 128^2 77 / 138 vs 85 / 150,
-//            16 x 64^2 65 / 114 vs 81 / 137, 256^2 98 / 173 vs 99 / 174,
-//            256 x 1024 (256 groups) 128 / 249 vs 140 / 263;
+//   float64  64^2 63 / 111 vs 75 / 137, 128^2 78 / 138 vs 85 / 150,
+//            16 x 64^2 66 / 115 vs 81 / 137, 256^2 98 / 173 vs 99 / 174,
+//            256 x 1024 (256 groups) 131 / 251 vs 140 / 263;
 //   beyond:  16 x 128^2 (512 groups) 112 / 211 vs 106 / 196, 16 x 256^2 305 / 529 vs
 //            236 / 457, 400 x 300 115 / 201 vs 108 / 197, float32 512^2 123 / 235 vs
 //            116 / 209.

@@ -544,8 +544,9 @@ __global__ __launch_bounds__(TX * TY) void k_stage_vjp_zm(Grid g, const T* __res
                         pu[s][c] = T(double(wb[c * nc + j]) - (pb[jp[c]] - pc) * g.ih[c]);
                     else
                         pu[s][c] = wb[c * nc + j];
-                    T fv = cb * yb[c * nc + j];
-                    if constexpr (HAS_W) fv = fma(cw, T(double(ub[c * nc + j]) - (qb[jp[c]] - qc) * g.ih[c]), fv);
+                    T fv;
+                    if constexpr (HAS_W) fv = fma(cb, yb[c * nc + j], cw * T(double(ub[c * nc + j]) - (qb[jp[c]] - qc) * g.ih[c]));
+                    else fv = cb * yb[c * nc + j];
                     pf[s][c] = fv;
                 }
             }
