@@ -175,8 +175,9 @@ const char* ins_last_error(void);
  * solver), from p = 0, for A p = mean(r) - r, independently per batch field.
  * A field stops once ||res|| <= rtol ||res_0|| (res the recursively updated
  * residual) or after maxiter iterations. A field that fits on the chip (about
- * 500,000 cells) is solved by one launch, which stops by itself (check_every is
- * not used). Otherwise iterations run back to back on the
+ * 500,000 cells) is solved within one launch, which stops by itself (check_every is
+ * not used; see ins_cg_set_wait). Fields of a batch share a launch as far as the chip
+ * holds them. Otherwise iterations run back to back on the
  * stream; every check_every iterations the call reads the convergence flags
  * to the host once (a stream synchronisation), and stops launching when all
  * fields are done. check_every = 0 never synchronises and always launches

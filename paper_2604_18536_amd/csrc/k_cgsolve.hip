@@ -7,8 +7,8 @@
 // field 13 + 10 us, for 0.1-6 MB of data: launch, fill and drain, and every
 // workgroup's re-reduction of the partial sums. What bounds it here is latency:
 // that of the sums, and of the stencil's LDS reads at 2 waves per SIMD. Per iteration
-// (before -> now, one step's four solves): 64^2 12 -> 1.6 us, 128^2 2.8, 32^3 3.2,
-// 70 x 63 x 54 23.5 -> 5.8, the channel 66 x 81 x 48 24 -> 6.1, 79^3 26 -> 11 us.
+// (two kernels -> one launch): 64^2 11.5 -> 1.6 us, 128^2 12 -> 2.7, 33 x 32 x 32 13.3 ->
+// 3.0, 70 x 63 x 54 23 -> 5.65, the channel 66 x 81 x 48 24 -> 6.0, 79^3 26 -> 10 us.
 //
 // One workgroup (fields of at most 4096 cells): the recurrence, stop test and sums
 // of k_cg.hpp, two sums per iteration. Several workgroups: one exchange per
@@ -31,21 +31,21 @@
 //
 // The fields of a batch run side by side, as many per launch as the chip holds
 // (128^2, us per iteration for 1 / 16 / 256 fields: 2.7 / 3.5 / 55; one field after
-// another 2.75 / 44 / 705; the two-kernel iteration 12 / 14 / 93). The workgroups
-// of a field have to be resident together. The launch is cooperative, which sees to
-// that; one recorded into a graph replays as a plain one, and there workgroups take
-// their field and block in the order in which they start (`ordered`). Those that run then form
-// whole fields, and a launch has at most one field that waits for workgroups still to
-// start, with at most kCgMaxGroups - 1 = 63 of them on the chip: launches on four
-// hardware queues keep 252 workgroups waiting, fewer than there are CUs, so the next
-// one to start always finds room. (Their order of start places neighbouring blocks
-// worse: 8 fields of 41 x 40 x 40 9.5 us per iteration instead of 9.0, 64 of 128^2
-// 15.7 instead of 13.7.) Neither
-// says anything of other processes on the same GPU, so every wait is bounded: past
-// the bound a workgroup marks its field (CgScal::failed) and leaves, the others
-// follow, and k_cg_alone, launched behind every such solve, solves a marked field
-// again from r_0 with one workgroup, which waits for nobody. The caller gets a
-// solved field either way.
+// another 2.75 / 44 / 705; the two-kernel iteration 12 / 14 / 93).
+//
+// The workgroups of a field have to be resident together. The launch is cooperative,
+// which sees to that. One recorded into a graph replays as a plain one: there
+// workgroups take their field and block in the order in which they start (`ordered`).
+// Those that run then form whole fields, and a launch has at most one field that waits
+// for workgroups still to start, with at most kCgMaxGroups - 1 = 63 of them on the chip:
+// launches on four hardware queues keep 252 workgroups waiting, fewer than there are
+// CUs, so the next one to start always finds room. (The order of start places
+// neighbouring blocks worse: 8 fields of 41 x 40 x 40 9.5 us per iteration instead of
+// 9.0, 64 of 128^2 15.7 instead of 13.7.) Neither says anything of other processes on the
+// same GPU, so every wait is bounded: past the bound a workgroup marks its field
+// (CgScal::failed) and leaves, the others follow, and k_cg_alone, launched behind every
+// such solve, solves a marked field again from r_0 with one workgroup, which waits for
+// nobody. The caller gets a solved field either way.
 #include <algorithm>
 
 #include "k_cg.hpp"
